@@ -171,10 +171,8 @@ sqn_status sqn_create_linear_caches(const sqn_cache_desc* desc,
  * Unlike sqn_create_caches the call does not wait: the input arrays must
  * stay valid, and no render with the handle may run on another stream, until
  * the stream has finished the call's work; renders on `stream` after it see
- * the new caches.  The preparation uses a 20 MiB scratch array that each
- * device holds for the life of the process and that every call on that
- * device shares: calls on one device that overlap in time (two streams, two
- * threads) race on it and must be serialised by the caller.
+ * the new caches.  The preparation's scratch lies in the handle's own block,
+ * so calls on different handles may overlap.
  * Errors: SQN_ERR_INVALID_ARG (NULL, range, n_p > 2048, a layout larger than
  * the handle's block, input arrays that are not device allocations large
  * enough, wrong device), SQN_ERR_UNSUPPORTED (a handle made by

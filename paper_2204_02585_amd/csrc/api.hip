@@ -9,7 +9,6 @@
 
 #include <algorithm>
 #include <limits>
-#include <mutex>
 #include <vector>
 
 #include "sqn_internal.h"
@@ -199,7 +198,7 @@ sqn_status validate_decoder(const sqn_linear_decoder* dec, int32_t D)
 {
     if (!dec)
         return fail(SQN_ERR_INVALID_ARG, "decoder is NULL");
-    if (dec->d_sigma < 1 || dec->d_sigma > 64)
+    if (dec->d_sigma < 1 || dec->d_sigma > sqn::kMaxSigma)
         return fail(SQN_ERR_INVALID_ARG, "d_sigma = %d outside [1, 64]", dec->d_sigma);
     if (!dec->w_sigma || !dec->w_uvw || !dec->b_uvw)
         return fail(SQN_ERR_INVALID_ARG, "decoder weight pointer is NULL");
@@ -401,6 +400,115 @@ CacheLayout cache_layout(const sqn_cache_desc* desc, bool linear)
     return L;
 }
 
+// Scratch of the preparation: its size and, from a base address, its parts.
+size_t prepare_work(const sqn_cache_desc* desc, bool linear, char* base, sqn::PrepareWork* pw)
+{
+    size_t total = 0;
+    auto take = [&](size_t n) {
+        char* at = base + total;
+        total += align256(n);
+        return at;
+    };
+    memset(pw, 0, sizeof(*pw));
+    pw->f = reinterpret_cast<uint8_t*>(take(sqn::prepare_f_bytes(desc->n_p)));
+    pw->f_min = reinterpret_cast<uint8_t*>(take(sqn::prepare_f_min_bytes(desc->n_p)));
+    if (linear) {
+        const size_t n_p = static_cast<size_t>(desc->n_p), m = static_cast<size_t>(sqn::linear_cells(desc->n_p));
+        pw->s = reinterpret_cast<float*>(take(3 * n_p * n_p * sizeof(float)));
+        pw->part = reinterpret_cast<float*>(take(sqn::prepare_part_floats(desc->n_p) * sizeof(float)));
+        pw->maxima = reinterpret_cast<float*>(take(6 * n_p * sizeof(float)));
+        pw->cell_max = reinterpret_cast<float*>(take(3 * m * m * sizeof(float)));
+        pw->cell_part = reinterpret_cast<uint8_t*>(take(m * m * 128));
+    }
+    return total;
+}
+
+// Bytes from the start of the uvw planes to the end of the direction cache in
+// a handle's block.  The copies fill them last, so until then the preparation
+// takes its scratch there: no second allocation on a load (hipMalloc and
+// hipFree of one cost 60-100 us of a 512 cache's 430), and none at all on a
+// recreate.  It fits unless a linear decoder has few components (D = 1) or a
+// small grid.
+size_t late_bytes(const CacheLayout& lay) { return lay.off_lin - lay.off_uvw[0]; }
+
+// ---- copies ------------------------------------------------------------------
+
+struct CopyArgs {
+    const uint4* src[4];
+    uint4* dst[4];
+    size_t n[4];              // whole 16-byte pieces
+    uint32_t tail[4];         // 2-byte values after them, fewer than 8
+};
+
+// Array blockIdx.y, kCopyPieces 16-byte pieces per thread, every workgroup a
+// run of its own.  157 MB in 66 us, 4.8 TB/s of reads and writes together,
+// against 67 us for four runtime copies back to back.  Sharing a launch with
+// column_pack (its workgroups first) took 108 us for the two, against 85 us
+// apart: at that kernel's 104 registers half as many copying waves fit.
+constexpr int32_t kCopyPieces = 8;
+__global__ __launch_bounds__(256) void copy_arrays(const CopyArgs A)
+{
+    const int32_t y = blockIdx.y;
+    const uint4* src = y == 0 ? A.src[0] : (y == 1 ? A.src[1] : (y == 2 ? A.src[2] : A.src[3]));
+    uint4* dst = y == 0 ? A.dst[0] : (y == 1 ? A.dst[1] : (y == 2 ? A.dst[2] : A.dst[3]));
+    const size_t n = y == 0 ? A.n[0] : (y == 1 ? A.n[1] : (y == 2 ? A.n[2] : A.n[3]));
+    const size_t first = static_cast<size_t>(blockIdx.x) * (256 * kCopyPieces) + threadIdx.x;
+    if (blockIdx.x == 0) {
+        const uint32_t tail = y == 0 ? A.tail[0] : (y == 1 ? A.tail[1] : (y == 2 ? A.tail[2] : A.tail[3]));
+        if (threadIdx.x < tail)
+            reinterpret_cast<uint16_t*>(dst + n)[threadIdx.x]
+                = reinterpret_cast<const uint16_t*>(src + n)[threadIdx.x];
+    }
+    if (first - threadIdx.x + 256 * kCopyPieces <= n) {
+        // a whole run: all its loads in flight before the first store
+        uint4 v[kCopyPieces];
+#pragma unroll
+        for (int32_t k = 0; k < kCopyPieces; ++k)
+            v[k] = src[first + 256 * k];
+#pragma unroll
+        for (int32_t k = 0; k < kCopyPieces; ++k)
+            dst[first + 256 * k] = v[k];
+    } else {
+        for (int32_t k = 0; k < kCopyPieces; ++k)
+            if (first + 256 * k < n)
+                dst[first + 256 * k] = src[first + 256 * k];
+    }
+}
+
+// The uvw planes and the direction cache into the handle's block.
+hipError_t copy_uvw_beta(const void* const uvw[3], const void* beta, char* base, const CacheLayout& lay,
+                         hipStream_t stream)
+{
+    const void* const src[4] = {uvw[0], uvw[1], uvw[2], beta};
+    char* const dst[4] = {base + lay.off_uvw[0], base + lay.off_uvw[1], base + lay.off_uvw[2], base + lay.off_beta};
+    const size_t bytes[4] = {lay.uvw_bytes, lay.uvw_bytes, lay.uvw_bytes, lay.beta_bytes};
+    CopyArgs args;
+    size_t most = 0;
+    bool aligned = true;
+    for (int k = 0; k < 4; ++k) {
+        args.src[k] = static_cast<const uint4*>(src[k]);
+        args.dst[k] = reinterpret_cast<uint4*>(dst[k]);
+        args.n[k] = bytes[k] / 16;
+        args.tail[k] = static_cast<uint32_t>(bytes[k] % 16 / 2);
+        most = args.n[k] > most ? args.n[k] : most;
+        aligned = aligned && (reinterpret_cast<uintptr_t>(src[k]) & 15u) == 0;
+    }
+    // the kernel moves 16-byte pieces (the block's regions are 256-byte
+    // aligned); arrays that start between them go through the
+    // runtime's copy
+    if (!aligned) {
+        for (int k = 0; k < 4; ++k) {
+            const hipError_t e = hipMemcpyAsync(dst[k], src[k], bytes[k], hipMemcpyDeviceToDevice, stream);
+            if (e != hipSuccess)
+                return e;
+        }
+        return hipSuccess;
+    }
+    constexpr size_t per = 256 * kCopyPieces;
+    copy_arrays<<<dim3(static_cast<uint32_t>(most / per + 1), 4), 256, 0, stream>>>(args);
+    return hipGetLastError();
+}
+
 // Shared body of the two create calls; dec == NULL selects Eq. 4.
 sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec,
                        const void* const sigma_planes[3], const void* const uvw_planes[3],
@@ -427,7 +535,6 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     const size_t lin_rows = 9 * static_cast<size_t>(D) + 3;
     const int32_t cell_shift = sqn::linear_cell_shift(desc->n_p);
     const int32_t cell_m = sqn::linear_cells(desc->n_p);
-    const size_t cells = lay.cells;
     static const char* names_s[3] = {"sigma_planes[0] (xy)", "sigma_planes[1] (yz)", "sigma_planes[2] (zx)"};
     static const char* names_u[3] = {"uvw_planes[0] (xy)", "uvw_planes[1] (yz)", "uvw_planes[2] (zx)"};
     for (int j = 0; j < 3; ++j) {
@@ -439,38 +546,14 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     if ((s = check_device_range(beta, beta_bytes, "beta")) != SQN_OK)
         return s;
 
-    auto align = align256;
     const size_t* off_sigma = lay.off_sigma;
     const size_t* off_uvw = lay.off_uvw;
     const size_t off_beta = lay.off_beta, off_lin = lay.off_lin, off_cells = lay.off_cells, total = lay.total;
 
-    // temporary buffers of the preparation, freed before returning
-    size_t work_total = 0;
-    const size_t w_live = work_total;
-    work_total += align(texels);
-    const size_t w_f = work_total;
-    work_total += align(texels * sizeof(uint16_t));
-    const size_t w_dist = work_total;
-    work_total += align(texels * sizeof(uint16_t));
-    const size_t w_max = work_total;
-    work_total += align(6 * static_cast<size_t>(desc->n_p) * sizeof(float));
-    const size_t w_ws = work_total;
-    work_total += align(3 * static_cast<size_t>(ds) * sizeof(float));
-    const size_t w_cmax = work_total;
-    work_total += align(3 * static_cast<size_t>(cell_m) * cell_m * sizeof(float));
-    const size_t w_clive = work_total;
-    work_total += align(cells);
-    const size_t w_cf = work_total;
-    work_total += align(cells * sizeof(uint16_t));
-    const size_t w_cf2 = work_total;
-    work_total += align(cells * sizeof(uint16_t));
-    const size_t w_rows = work_total;
-    work_total += align(linear ? texels * sizeof(uint2) : 0);
-
-    // host-side parameters of the linear decoder: W_sigma, and the radiance
-    // weights transposed so that row c*3D + e holds W_c[0..D)[e], followed
+    // host-side parameters of the linear decoder: the radiance weights
+    // transposed so that row c*3D + e holds W_c[0..D)[e], followed
     // by the rows b_u, b_v, b_w
-    std::vector<float> lin_host, ws_host;
+    std::vector<float> lin_host;
     if (linear) {
         lin_host.resize(lin_rows * D);
         for (int32_t c = 0; c < 3; ++c)
@@ -481,7 +564,6 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
         for (int32_t c = 0; c < 3; ++c)
             for (int32_t d = 0; d < D; ++d)
                 lin_host[(9 * static_cast<size_t>(D) + c) * D + d] = dec->b_uvw[c * D + d];
-        ws_host.assign(dec->w_sigma, dec->w_sigma + 3 * ds);
     }
 
     sqn_caches* h = static_cast<sqn_caches*>(calloc(1, sizeof(sqn_caches)));
@@ -505,25 +587,21 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     h->bytes = total;
     char* base = static_cast<char*>(h->block);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    char* work = nullptr;
-    e = hipMalloc(reinterpret_cast<void**>(&work), work_total);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipFree(h->block);
-        free(h);
-        return fail(SQN_ERR_OUT_OF_MEMORY, "hipMalloc of %zu scratch bytes failed", work_total);
-    }
+    // scratch of the preparation, an allocation of its own (freed before
+    // returning) only where the block has no room for it
     sqn::PrepareWork pw;
-    pw.live = reinterpret_cast<uint8_t*>(work + w_live);
-    pw.f = reinterpret_cast<uint16_t*>(work + w_f);
-    pw.dist = reinterpret_cast<uint16_t*>(work + w_dist);
-    pw.maxima = reinterpret_cast<float*>(work + w_max);
-    pw.w_sigma = reinterpret_cast<float*>(work + w_ws);
-    pw.cell_max = reinterpret_cast<float*>(work + w_cmax);
-    pw.cell_live = reinterpret_cast<uint8_t*>(work + w_clive);
-    pw.cell_f = reinterpret_cast<uint16_t*>(work + w_cf);
-    pw.cell_f2 = reinterpret_cast<uint16_t*>(work + w_cf2);
-    pw.rows = reinterpret_cast<uint2*>(work + w_rows);
+    char* work = nullptr;
+    const size_t work_total = prepare_work(desc, linear, base + off_uvw[0], &pw);
+    if (work_total > late_bytes(lay)) {
+        e = hipMalloc(reinterpret_cast<void**>(&work), work_total);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipFree(h->block);
+            free(h);
+            return fail(SQN_ERR_OUT_OF_MEMORY, "hipMalloc of %zu scratch bytes failed", work_total);
+        }
+        prepare_work(desc, linear, work, &pw);
+    }
 
     void* packed[3];
     for (int j = 0; j < 3; ++j) {
@@ -533,31 +611,22 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     }
     h->beta = base + off_beta;
     if (linear) {
-        e = hipMemcpyAsync(pw.w_sigma, ws_host.data(), ws_host.size() * sizeof(float),
-                           hipMemcpyHostToDevice, st);
+        e = hipMemcpyAsync(base + off_lin, lin_host.data(), lin_bytes, hipMemcpyHostToDevice, st);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(base + off_lin, lin_host.data(), lin_bytes, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = sqn::prepare_linear_planes(sigma_planes, desc->sigma_dtype, desc->n_p, ds, dec->b_sigma,
-                                           packed, pw, st);
-        if (e == hipSuccess)
-            e = sqn::prepare_linear_cells(packed, desc->n_p, dec->b_sigma, cell_shift, cell_m,
-                                          reinterpret_cast<uint8_t*>(base + off_cells), pw, st);
-        if (e == hipSuccess)
-            e = sqn::interleave_linear_planes(packed, desc->n_p, pw, st);
+            e = sqn::prepare_linear_planes(sigma_planes, desc->sigma_dtype, desc->n_p, ds, dec->w_sigma, dec->b_sigma,
+                                           packed, cell_shift, cell_m, reinterpret_cast<uint8_t*>(base + off_cells),
+                                           pw, st);
     } else {
-        for (int j = 0; j < 3 && e == hipSuccess; ++j)
-            e = sqn::prepare_sigma_plane(sigma_planes[j], desc->sigma_dtype, desc->n_p, packed[j], pw, st);
+        e = sqn::prepare_sigma_planes(sigma_planes, desc->sigma_dtype, desc->n_p, packed, pw, st);
     }
-    for (int j = 0; j < 3 && e == hipSuccess; ++j)
-        e = hipMemcpyAsync(base + off_uvw[j], uvw_planes[j], uvw_bytes, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(base + off_beta, beta, beta_bytes, hipMemcpyDeviceToDevice, st);
+        e = copy_uvw_beta(uvw_planes, beta, base, lay, st);
     if (e == hipSuccess)
         e = hipStreamSynchronize(st);
     else
         (void)hipStreamSynchronize(st);
-    (void)hipFree(work);
+    if (work)
+        (void)hipFree(work);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(h->block);
@@ -582,47 +651,8 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     return SQN_OK;
 }
 
-// ---- sqn_recreate_caches: create-time preparation without allocating -------
-//
-// The distance transform of a plane needs n_p^2 bytes of live mask and two
-// n_p^2 arrays of uint16 (row and capped Chebyshev distances).  For callers
-// that cannot allocate, that scratch lives in one file-scope device array,
-// sized for n_p <= kRecreateMaxNp.  Every device the library runs on holds
-// its own copy until the process ends.  In host code `scratch` names a host
-// stand-in, not device memory: its device address is taken once per device
-// with hipGetSymbolAddress and only that address is passed to kernels.
-
+// The largest grid sqn_recreate_caches takes.
 constexpr int32_t kRecreateMaxNp = 2048;
-constexpr size_t kRecreateScratchBytes = 5 * static_cast<size_t>(kRecreateMaxNp) * kRecreateMaxNp;
-static_assert(kRecreateScratchBytes == 20u << 20, "20 MiB of scratch");
-
-__device__ __align__(256) uint8_t scratch[kRecreateScratchBytes];
-
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mutex;
-void* g_scratch_ptr[kMaxDevices];   // device address of `scratch` per device
-
-// Device address of `scratch` on the current device `device`, looked up on
-// the first call for that device.
-sqn_status scratch_address(int device, void** out)
-{
-    if (device < 0 || device >= kMaxDevices)
-        return fail(SQN_ERR_UNSUPPORTED, "device %d is beyond the %d devices this library tracks", device,
-                    kMaxDevices);
-    std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (!g_scratch_ptr[device]) {
-        void* p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || p == nullptr) {
-            (void)hipGetLastError();
-            return fail(SQN_ERR_DEVICE, "hipGetSymbolAddress(scratch) failed on device %d: %s", device,
-                        hipGetErrorString(e));
-        }
-        g_scratch_ptr[device] = p;
-    }
-    *out = g_scratch_ptr[device];
-    return SQN_OK;
-}
 
 // ---- cache generation: networks on the host side ---------------------------
 
@@ -754,8 +784,8 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     if (!sigma_planes || !uvw_planes)
         return fail(SQN_ERR_INVALID_ARG, "plane pointer array is NULL");
     if (desc->n_p > kRecreateMaxNp)
-        return fail(SQN_ERR_INVALID_ARG, "n_p = %d exceeds %d, the largest grid the static scratch (%zu bytes) covers",
-                    desc->n_p, kRecreateMaxNp, kRecreateScratchBytes);
+        return fail(SQN_ERR_INVALID_ARG, "n_p = %d exceeds %d, the largest grid the preparation's scratch covers",
+                    desc->n_p, kRecreateMaxNp);
     int device = -1;
     if (hipGetDevice(&device) != hipSuccess)
         return fail(SQN_ERR_DEVICE, "hipGetDevice failed");
@@ -777,28 +807,19 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     }
     if ((s = check_device_range(beta, lay.beta_bytes, "beta")) != SQN_OK)
         return s;
-    void* scr = nullptr;
-    if ((s = scratch_address(device, &scr)) != SQN_OK)
-        return s;
 
-    // live mask, row distances and capped distances of one plane at a time;
-    // every kernel of the preparation writes its whole array before it is
-    // read, so nothing needs clearing
-    sqn::PrepareWork pw;
-    memset(&pw, 0, sizeof(pw));
-    uint8_t* w = static_cast<uint8_t*>(scr);
-    pw.live = w;
-    pw.f = reinterpret_cast<uint16_t*>(w + align256(texels));
-    pw.dist = reinterpret_cast<uint16_t*>(w + align256(texels) + align256(texels * sizeof(uint16_t)));
+    // the scratch lies where the uvw planes and the direction cache go; every
+    // kernel of the preparation writes its whole array before it is read, so
+    // nothing needs clearing
     char* base = static_cast<char*>(caches->block);
+    sqn::PrepareWork pw;
+    if (prepare_work(desc, false, base + lay.off_uvw[0], &pw) > late_bytes(lay))
+        return fail(SQN_ERR_UNSUPPORTED, "the preparation's scratch does not fit the handle's block");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = hipSuccess;
-    for (int j = 0; j < 3 && e == hipSuccess; ++j)
-        e = sqn::prepare_sigma_plane(sigma_planes[j], desc->sigma_dtype, desc->n_p, base + lay.off_sigma[j], pw, st);
-    for (int j = 0; j < 3 && e == hipSuccess; ++j)
-        e = hipMemcpyAsync(base + lay.off_uvw[j], uvw_planes[j], lay.uvw_bytes, hipMemcpyDeviceToDevice, st);
+    void* const packed[3] = {base + lay.off_sigma[0], base + lay.off_sigma[1], base + lay.off_sigma[2]};
+    hipError_t e = sqn::prepare_sigma_planes(sigma_planes, desc->sigma_dtype, desc->n_p, packed, pw, st);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(base + lay.off_beta, beta, lay.beta_bytes, hipMemcpyDeviceToDevice, st);
+        e = copy_uvw_beta(uvw_planes, beta, base, lay, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SQN_ERR_DEVICE, "cache preparation failed (the handle's contents are now unspecified): %s",

@@ -79,47 +79,43 @@ constexpr int32_t kDistCap = 255;
 
 // Temporary device buffers of the create-time preparation.
 struct PrepareWork {
-    uint8_t* live;        // [n_p^2] 1 where a texel may give sigma > 0
-    uint16_t* f;          // [n_p^2] row distances
-    uint16_t* dist;       // [n_p^2] capped Chebyshev distances
+    uint8_t* f;           // prepare_f_bytes(n_p): row distances of the three planes
+    uint8_t* f_min;       // prepare_f_min_bytes(n_p): their minima over 16 rows
+    // linear decoder
+    float* s;             // [3][n_p][n_p] partial sums
+    float* part;          // prepare_part_floats(n_p): maxima of runs of rows and columns
     float* maxima;        // [6][n_p] row / column maxima of the partial sums
-    float* w_sigma;       // [3 d_sigma] density weights (linear decoder)
-    float* cell_max;      // [3][m][m] per-plane cell maxima (linear decoder)
-    uint8_t* cell_live;   // [m^3]
-    uint16_t* cell_f;     // [m^3] partial distances
-    uint16_t* cell_f2;    // [m^3]
-    uint2* rows;          // [n_p^2] row-major copy of a linear decoder's plane
+    float* cell_max;      // [3][m][m] per-plane cell maxima
+    uint8_t* cell_part;   // [m][m][128] cell distances along two axes
 };
+size_t prepare_f_bytes(int32_t n_p);
+size_t prepare_f_min_bytes(int32_t n_p);
+size_t prepare_part_floats(int32_t n_p);
 
-// Pack sigma plane j (n_p x n_p of sigma_dtype, device memory) into
-// `packed` (4-byte records for binary16 sigma, 8-byte for binary32) with the
-// capped distance transform.
-hipError_t prepare_sigma_plane(const void* sigma, int sigma_dtype, int32_t n_p, void* packed,
-                               const PrepareWork& work, hipStream_t stream);
+// Most density channels of a linear decoder.
+constexpr int32_t kMaxSigma = 64;
+
+// Pack the three sigma planes (n_p x n_p of sigma_dtype, device memory) into
+// `packed` (4-byte records for binary16 sigma, 8-byte for binary32, four rows
+// interleaved) with the capped distance transform; uses work.f and work.f_min.
+hipError_t prepare_sigma_planes(const void* const sigma[3], int sigma_dtype, int32_t n_p, void* const packed[3],
+                                const PrepareWork& work, hipStream_t stream);
 
 // Linear (Eq. 5) decoder: fold each plane's sigma^j vectors
 // ([n_p][n_p][d_sigma] of sigma_dtype) with its block of W_sigma into
 // per-texel partial sums, mark the texels whose samples are empty whatever
 // the other two planes hold, and write 8-byte records (partial sum, capped
-// distance to the nearest texel not so marked) to packed[j].
-hipError_t prepare_linear_planes(const void* const sigma[3], int sigma_dtype, int32_t n_p,
-                                 int32_t d_sigma, float b_sigma, void* const packed[3],
-                                 const PrepareWork& work, hipStream_t stream);
-
-// Cell grid of the linear decoder (after prepare_linear_planes): cells of
-// g x g x g nodes (g = 2^shift), m = ceil(n_p / g) per axis; a cell is empty when
+// distance to the nearest texel not so marked; four rows interleaved) to
+// packed[j].  Then the cell grid: cells of g x g x g nodes (g = 2^cell_shift),
+// m = ceil(n_p / g) <= 128 per axis; a cell is empty when
 // ((M_xy + M_yz) + M_zx) + b_sigma <= 0 with M_j the largest partial sum of
 // plane j over the cell's footprint (binary32 addition is monotone), and
-// cell_dist[(cx m + cy) m + cz] receives the capped Chebyshev distance in
-// cells to the nearest cell not so marked.  work.cell_max holds 3 m^2
-// floats, work.cell_live m^3 bytes, work.cell_f / cell_g2 m^3 uint16 each.
-hipError_t prepare_linear_cells(const void* const packed[3], int32_t n_p, float b_sigma, int32_t shift,
-                                int32_t m, uint8_t* cell_dist, const PrepareWork& work, hipStream_t stream);
-
-// Move the linear decoder's packed planes (row-major after the passes
-// above) into the interleaved order the renderer reads, through work.rows.
-hipError_t interleave_linear_planes(void* const packed[3], int32_t n_p, const PrepareWork& work,
-                                    hipStream_t stream);
+// cell_dist[(cx m + cy) m + cz] receives the Chebyshev distance in cells to
+// the nearest cell not so marked (255: none).
+// `w_sigma` (3 d_sigma values) is host memory, read before the call returns.
+hipError_t prepare_linear_planes(const void* const sigma[3], int sigma_dtype, int32_t n_p, int32_t d_sigma,
+                                 const float* w_sigma, float b_sigma, void* const packed[3], int32_t cell_shift, int32_t m,
+                                 uint8_t* cell_dist, const PrepareWork& work, hipStream_t stream);
 
 // Cell side 2^shift for an n_p grid: the smallest power of two >= 2 that
 // leaves at most 128 cells per axis.
