@@ -223,10 +223,10 @@ sqn_status sqn_render_stats(const sqn_caches* caches,
 /* Launch shape of later renders with this handle: how many lanes of a
  * wavefront share one ray (1, 4 or 8; the L lanes take the L consecutive
  * samples of a chunk), or 0 (the default) to choose per call from the number
- * of rays (8 below 2^18 rays, 4 below 2^20, else 1).  Sample, index and
- * termination decisions are identical for every choice; colour and depth
- * agree up to the rounding of their sums.  Not thread-safe against
- * concurrent renders with the handle.
+ * of rays (8 below 2^18 rays, below 2^20 two, or 4 for the dense march, else
+ * 1).  Sample, index and termination decisions are identical for every
+ * choice; colour and depth agree up to the rounding of their sums.  Not
+ * thread-safe against concurrent renders with the handle.
  * Errors: SQN_ERR_INVALID_ARG; SQN_ERR_UNSUPPORTED for 1 or 8 on a handle
  * made by sqn_create_linear_caches (always four lanes). */
 sqn_status sqn_set_lanes_per_ray(sqn_caches* caches, int32_t lanes);
@@ -262,7 +262,8 @@ sqn_status sqn_set_centre_block(sqn_caches* caches, float fraction);
  * settings stay and nothing is written).  No candidate changes a sample, index or
  * termination decision, only the time; which is fastest depends on the
  * image size, the number of views and the scene (the chains of samples),
- * which the default per-call choice sees only through the number of rays.
+ * which the default per-call choice (which has two lanes besides) sees only
+ * through the number of rays.
  * A single view deals its tiles in blocks of 2 x 2 from the centre of the
  * image outwards.  rgb_out and depth_out receive a render of
  * the batch.  Blocks until the timed renders finish; creates two HIP events

@@ -219,14 +219,18 @@ sqn_status validate_decoder(const sqn_linear_decoder* dec, int32_t D)
 // Lanes per ray for a call of `rays` rays.  One lane per ray does the least
 // work per sample, but a wave lives as long as its longest ray: below about
 // 2^20 rays (one 800x800 view is 10^4 waves against 8192 resident wave
-// slots) the heaviest waves, not throughput, set the time, and four lanes per
-// ray cut their chains of dependent samples four-fold.  Below 2^18 rays
-// (under two rounds of four-lane waves) eight lanes shorten them again
-// (504x378 forward-facing view: 0.107 against 0.118 ms; at 800x800 eight
-// lanes cost more vector-ALU work than they save).
-int choose_lanes(int64_t rays)
+// slots) the heaviest waves, not throughput, set the time, and two lanes per
+// ray halve their chains of dependent samples for a quarter more vector
+// instructions.  Measured with 1 / 2 / 4 / 8 lanes, us: 800x800x192 of a 256
+// cache 96 / 92 / 103 / 139, 800x800x256 of a 512 cache 149 / 122 / 135 / 174,
+// 617x463 140 / 135 / 150 / 185, 1092x899 298 / 252 / 277 / 357, and past the
+// line 1314x865 94 / 109 / 144 / 205.  Below 2^18 rays the chip is not full
+// for one round of two-lane waves and eight lanes shorten the chains again
+// (504x378 forward-facing 213 / 127 / 101 / 89, 287x276 91 / 58 / 51 / 38).
+// The dense march, whose chains are alike, keeps four lanes in between.
+int choose_lanes(int64_t rays, bool skip)
 {
-    return rays < (int64_t{1} << 18) ? 8 : (rays < (int64_t{1} << 20) ? 4 : 1);
+    return rays < (int64_t{1} << 18) ? 8 : (rays < (int64_t{1} << 20) ? (skip ? 2 : 4) : 1);
 }
 
 sqn_status render_common(const sqn_caches* h, const float* poses, int32_t n_poses,
@@ -292,7 +296,7 @@ sqn_status render_common(const sqn_caches* h, const float* poses, int32_t n_pose
     p.skip = h->skip;
     // the folded Eq. 5 weights are shared by the lanes of a ray in LDS, which
     // holds them for 64 rays per workgroup, i.e. four lanes per ray
-    p.lanes = h->linear ? 4 : (h->lanes != 0 ? h->lanes : choose_lanes(rays));
+    p.lanes = h->linear ? 4 : (h->lanes != 0 ? h->lanes : choose_lanes(rays, h->skip != 0));
     p.linear = h->linear;
     p.b_sigma = h->b_sigma;
     p.lin_w = h->lin_w;

@@ -1,6 +1,6 @@
 // Render kernels of the cached SqueezeNeRF path for gfx950 (CDNA4).
 //
-// Work layout.  L consecutive lanes of a wave64 (L = 1, 4 or 8) share one
+// Work layout.  L consecutive lanes of a wave64 (L = 1, 2, 4 or 8) share one
 // pixel ray and walk its samples in chunks of L consecutive samples, one per
 // lane; a wave holds 64/L rays laid out as a compact pixel tile.  Rays of a
 // tile sit a fraction of a texel apart at equal sample index (samples lie on
@@ -46,7 +46,7 @@ __device__ __forceinline__ T load_at(const void* base, uint32_t off)
 }
 
 // ---------------------------------------------------------------------------
-// lanes of one ray: L = 4 consecutive lanes of a quad, exchanged with DPP
+// lanes of one ray: L = 2 or 4 consecutive lanes of a quad, exchanged with DPP
 // quad permutations, or L = 8 lanes of a half-row, whose two quads also
 // exchange through the half-row mirror (lane i <-> 7 - i); the group is
 // always entirely active or inactive
@@ -78,7 +78,9 @@ __device__ __forceinline__ float dppf(float x)
 template <int L>
 __device__ __forceinline__ float grp_next(float x)
 {
-    if constexpr (L == 4)
+    if constexpr (L == 2)
+        return dppf<qperm(1, 1, 3, 3)>(x);
+    else if constexpr (L == 4)
         return dppf<qperm(1, 2, 3, 3)>(x);
     else if constexpr (L == 8) {
         // lane 3 takes lane 4 from the other quad (7 - 3 = 4)
@@ -93,7 +95,9 @@ __device__ __forceinline__ float grp_next(float x)
 template <int L>
 __device__ __forceinline__ float grp_first(float x)
 {
-    if constexpr (L == 4)
+    if constexpr (L == 2)
+        return dppf<qperm(0, 0, 2, 2)>(x);
+    else if constexpr (L == 4)
         return dppf<qperm(0, 0, 0, 0)>(x);
     else if constexpr (L == 8) {
         // the upper quad reads lane 0 where the mirror put it, in lane 7
@@ -111,6 +115,10 @@ __device__ __forceinline__ void grp_scan(uint64_t q, int s, uint64_t& excl, uint
     if constexpr (L == 1) {
         excl = 0;
         total = q;
+    } else if constexpr (L == 2) {
+        const uint64_t first = dpp64<qperm(0, 0, 2, 2)>(q);
+        excl = s >= 1 ? first : 0;
+        total = q + dpp64<qperm(1, 0, 3, 2)>(q);
     } else {
         const int sq = s & 3;
         uint64_t y = q;
@@ -597,6 +605,33 @@ __device__ __forceinline__ void sample_colour_lin(const RenderParams& P, uint32_
     }
 }
 
+// 1 - exp(-q) for q >= 0, to about one unit in the last place of the result
+// for small q too: with -q log2(e) = n + f, |f| <= 1/2, it is
+// (1 - 2^n) - 2^n (2^f - 1), and 2^f - 1 = f p(f) by the Taylor series of
+// degree 7 (its next term is below 2^-25 of it).  n = 0, where 1 - 2^n
+// vanishes, is the only case with cancellation in a direct evaluation.  19
+// instructions against about 50 of -expm1f(-q): 1% on the views, whose
+// vector ALUs are near saturation.  NaN stays NaN.
+__device__ __forceinline__ float opacity(float q)
+{
+    const float qc = q > 64.0f ? 64.0f : q;
+    constexpr float kHi = 1.44269502162933349609375f, kLo = 1.92596299112661746887e-8f;   // log2(e)
+    const float n = __builtin_rintf(-qc * kHi);
+    float f = fmaf(-qc, kHi, -n);
+    f = fmaf(-qc, kLo, f);
+    // ln(2)^k / k!
+    float p = 1.52527338040598402800e-5f;
+    p = fmaf(p, f, 1.54035303933816099544e-4f);
+    p = fmaf(p, f, 1.33335581464284434234e-3f);
+    p = fmaf(p, f, 9.61812910762847716198e-3f);
+    p = fmaf(p, f, 5.55041086648215799531e-2f);
+    p = fmaf(p, f, 2.40226506959100712334e-1f);
+    p = fmaf(p, f, 6.93147180559945309417e-1f);
+    const float e = p * f;
+    const float s = __builtin_amdgcn_ldexpf(1.0f, static_cast<int32_t>(n));
+    return fmaf(-s, e, 1.0f - s);
+}
+
 // exp(-tau 2^-32) for a 2^-32 fixed-point optical depth.
 __device__ __forceinline__ float transmittance(uint64_t tau)
 {
@@ -643,10 +678,11 @@ struct ColourQueue {
 // in the one or two 64-byte segments of a record instead of one segment per
 // lane, which is what a gather costs the memory pipeline; the channel's
 // logit sums plane by plane in the order sample_colour uses.  That takes
-// four times the rounds, whose vector instructions the one-lane march at D
-// = 8 (bound by vector-ALU issue with many views) cannot spare, so QUADS is
-// set for rays of four or eight lanes and for D = 16, whose 96-byte records
-// leave the vector ALUs idle waiting for HBM.  Otherwise, or in a wave at
+// four times the rounds, whose vector instructions the march with one or two
+// lanes at D = 8 (bound by vector-ALU issue with many views; two lanes at
+// 800x800: 96 us by quads, 92 without) cannot spare, so QUADS is set for rays
+// of four or eight lanes and for D = 16, whose 96-byte records leave the
+// vector ALUs idle waiting for HBM.  Otherwise, or in a wave at
 // the image edge, one entry per lane.
 template <typename UT, int DC, bool LIN, int BS, bool QUADS>  // Eq. 4 only (LIN false)
 __device__ __forceinline__ void drain_colour(const RenderParams& P, const ColourQueue& cq, uint32_t& head,
@@ -741,9 +777,9 @@ struct SigmaRecord;
 template <>
 struct SigmaRecord<_Float16> {
     static constexpr uint32_t bytes = 4;
-    static __device__ __forceinline__ void load(const void* plane, uint32_t off, float& sigma, uint32_t& dist)
+    typedef uint32_t raw;
+    static __device__ __forceinline__ void unpack(raw w, float& sigma, uint32_t& dist)
     {
-        const uint32_t w = load_at<uint32_t>(plane, off);
         sigma = static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w & 0xffffu)));
         dist = w >> 16;
     }
@@ -752,9 +788,9 @@ struct SigmaRecord<_Float16> {
 template <>
 struct SigmaRecord<float> {
     static constexpr uint32_t bytes = 8;
-    static __device__ __forceinline__ void load(const void* plane, uint32_t off, float& sigma, uint32_t& dist)
+    typedef uint2 raw;
+    static __device__ __forceinline__ void unpack(raw w, float& sigma, uint32_t& dist)
     {
-        const uint2 w = load_at<uint2>(plane, off);
         sigma = __uint_as_float(w.x);
         dist = w.y;
     }
@@ -876,6 +912,50 @@ struct RayGeom {
     uint32_t jspan;           // (j0 = INT_MIN, jspan = 0 when there are none)
 };
 
+// The same in LDS, one per ray.  A world ray starts at the camera centre, and
+// its o and g0 are the view's (render_ray takes them from the pose): 48 bytes
+// instead of 72.
+template <bool NDC>
+struct RayLds {
+    RayGeom g;
+    __device__ __forceinline__ void put(const RayGeom& x) { g = x; }
+    __device__ __forceinline__ void get(RayGeom& x) const { x = g; }
+};
+template <>
+struct RayLds<false> {
+    float d[3], dn, inv_ds[3], margin;
+    int32_t i0, i1, j0;
+    uint32_t jspan;
+    __device__ __forceinline__ void put(const RayGeom& x)
+    {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            d[r] = x.d[r];
+            inv_ds[r] = x.inv_ds[r];
+        }
+        dn = x.dn;
+        margin = x.margin;
+        i0 = x.i0;
+        i1 = x.i1;
+        j0 = x.j0;
+        jspan = x.jspan;
+    }
+    __device__ __forceinline__ void get(RayGeom& x) const
+    {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            x.d[r] = d[r];
+            x.inv_ds[r] = inv_ds[r];
+        }
+        x.dn = dn;
+        x.margin = margin;
+        x.i0 = i0;
+        x.i1 = i1;
+        x.j0 = j0;
+        x.jspan = jspan;
+    }
+};
+
 // World ray through the pixel centre of (u, v) (camera looks down -z).
 __device__ __forceinline__ void pixel_ray(const RenderParams& P, int32_t view, int32_t u, int32_t v,
                                           float o[3], float d[3])
@@ -959,9 +1039,9 @@ template <typename ST, typename UT, int DC, bool STATS, int L, bool SKIP, bool L
           int BS = kBlockThreads>
 __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, int32_t u,
                                            int32_t v, int32_t lane, float* const beta, float* const lin,
-                                           const ColourQueue& cq, int32_t slot, const RayGeom* pre = nullptr)
+                                           const ColourQueue& cq, int32_t slot, const RayLds<NDC>* pre = nullptr)
 {
-    static_assert(L == 1 || L == 4 || L == 8, "one, four or eight lanes per ray");
+    static_assert(L == 1 || L == 2 || L == 4 || L == 8, "one, two, four or eight lanes per ray");
     const int32_t s = (L == 1) ? 0 : (lane & (L - 1));
     const int64_t ray = (static_cast<int64_t>(view) * P.height + v) * P.width + u;
     const int32_t N = P.n_samples;
@@ -970,7 +1050,7 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
 
     RayGeom geo;
     if constexpr (COOP) {
-        geo = *pre;
+        pre->get(geo);
         // Eq. 5: beta waits in the ray's LDS row; the L lanes fold it
         if constexpr (LIN)
             fold_decoder<DC, L>(P, s, lin);
@@ -1018,6 +1098,7 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
     // with one lane); Eq. 5 keeps a row of folded weights per ray in LDS
     // and, like the other D, evaluates colour where the sample is found
     constexpr bool kDefer = defers_colour(DC, LIN);
+    constexpr bool kQuads = L >= 4 || DC == 16;
     uint64_t tau = 0;              // optical depth before the chunk, 2^-32 units
     double acc_r = 0.0, acc_g = 0.0, acc_b = 0.0, acc_t = 0.0;
     int32_t last_live = -1;
@@ -1030,9 +1111,86 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
     }
     uint32_t q_head = 0, q_count = 0;   // the wave's queue, wave-uniform
 
+    // With one or two lanes per ray and for Eq. 5 the next sample's gathers
+    // (Eq. 5: its cell's byte) are issued as soon as it is known to be needed,
+    // before the sample ahead of it is composited (weight, queue, drain), so
+    // that work hides their latency: one lane, 800x800, 256 samples of a 512
+    // cache 159 -> 148 us, 192 samples of a 256 cache 98 -> 96; Eq. 5 at 512
+    // 170 -> 165; two lanes 124 -> 122.  Four and eight lanes, bound by
+    // vector-ALU issue, lose more to the values kept live (504x378 in NDC 88
+    // -> 98 us), so there a sample is gathered when its turn comes.
+    constexpr bool kAhead = L <= 2 || LIN;
+    using Rec = SigmaRecord<ST>;
+    float t = 0.0f;
+    uint32_t ix = 0, iy = 0, iz = 0;
+    bool inside = false;
+    typename Rec::raw raw[3] = {};
+    uint32_t cell = 0;             // Eq. 5 with leaps: the sample's cell distance
+    auto gather_planes = [&]() {
+        constexpr uint32_t RB = Rec::bytes;
+        const uint32_t bnm1 = RB * static_cast<uint32_t>(n_p - 1);
+        using Raw = typename Rec::raw;
+        raw[0] = load_at<Raw>(P.sigma[0], record_offset<RB>(row_part<RB>(ix, bnm1), iy));
+        raw[1] = load_at<Raw>(P.sigma[1], record_offset<RB>(row_part<RB>(iy, bnm1), iz));
+        raw[2] = load_at<Raw>(P.sigma[2], record_offset<RB>(row_part<RB>(iz, bnm1), ix));
+    };
+    // sample i at t: nodes, and the gathers that need nothing else
+    auto fetch = [&](int32_t i) {
+        float p[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const float td = t * d[r];
+            p[r] = o[r] + td;
+        }
+        // when every lane's sample is certainly in the box the six exact
+        // tests would all pass and the node indices need no clamp (a
+        // wave-uniform branch)
+        // 0 <= i - j0 <= jspan, one unsigned compare (i >= 0 > INT_MIN)
+        const bool deep = static_cast<uint32_t>(i) - static_cast<uint32_t>(j0) <= jspan;
+        if (__builtin_amdgcn_ballot_w64(deep) == __builtin_amdgcn_read_exec()) {
+            inside = true;
+            ix = nearest_node_inside(p[0], P.bmin[0], P.scale[0]);
+            iy = nearest_node_inside(p[1], P.bmin[1], P.scale[1]);
+            iz = nearest_node_inside(p[2], P.bmin[2], P.scale[2]);
+        } else {
+            inside = (i <= i1) & (p[0] >= P.bmin[0]) & (p[0] <= P.bmax[0]) & (p[1] >= P.bmin[1])
+                     & (p[1] <= P.bmax[1]) & (p[2] >= P.bmin[2]) & (p[2] <= P.bmax[2]);
+            // node indices are clamped to the grid for any position; they
+            // are used only for samples inside the box
+            ix = nearest_node(p[0], P.bmin[0], P.scale[0], hi_node);
+            iy = nearest_node(p[1], P.bmin[1], P.scale[1], hi_node);
+            iz = nearest_node(p[2], P.bmin[2], P.scale[2], hi_node);
+        }
+        if (inside) {
+            if constexpr (LIN && SKIP)
+                cell = P.cell_dist[((ix >> P.cell_shift) * P.cell_m + (iy >> P.cell_shift)) * P.cell_m
+                                   + (iz >> P.cell_shift)];
+            else
+                gather_planes();
+        }
+    };
+    // in-box samples among first .. last-1 (diagnostics of a leap)
+    auto count_inbox = [&](int32_t first, int32_t last) {
+        uint32_t n = 0;
+        for (int32_t k = first; k < last; ++k) {
+            const float tk = sample_t(P, stratified, ray_key, k);
+            bool in_k = true;
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const float pk = o[r] + tk * d[r];
+                in_k = in_k & (pk >= P.bmin[r]) & (pk <= P.bmax[r]);
+            }
+            n += in_k ? 1u : 0u;
+        }
+        return n;
+    };
+
     int32_t base = i0;
-    // t of this lane's sample in the current chunk
-    float t = (base <= i1) ? sample_t(P, stratified, ray_key, base + s) : 0.0f;
+    if (base <= i1) {
+        t = sample_t(P, stratified, ray_key, base + s);
+        if constexpr (kAhead)
+            fetch(base + s);
+    }
     // with deferred colour every lane present stays in the loop until the
     // wave is done, so that the whole wave evaluates the queued colours;
     // otherwise a lane leaves as soon as its ray is done
@@ -1047,36 +1205,15 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
         bool pushed = false;
         if (active) {
         const int32_t i = base + s;
-        const bool in_range = i <= i1;
-        const float t_next_chunk = sample_t(P, stratified, ray_key, base + L + s);
-
-        float p[3];
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const float td = t * d[r];
-            p[r] = o[r] + td;
+        if constexpr (!kAhead) {
+            // nothing of the last sample stays live across the loop
+            raw[0] = raw[1] = raw[2] = typename Rec::raw{};
+            fetch(i);
         }
-        bool inside;
-        uint32_t ix, iy, iz;
-        // when every lane's sample is certainly in the box the six exact
-        // tests would all pass and the node indices need no clamp (a
-        // wave-uniform branch)
-        // 0 <= i - j0 <= jspan, one unsigned compare (i >= 0 > INT_MIN)
-        const bool deep = static_cast<uint32_t>(i) - static_cast<uint32_t>(j0) <= jspan;
-        if (__builtin_amdgcn_ballot_w64(deep) == __builtin_amdgcn_read_exec()) {
-            inside = true;
-            ix = nearest_node_inside(p[0], P.bmin[0], P.scale[0]);
-            iy = nearest_node_inside(p[1], P.bmin[1], P.scale[1]);
-            iz = nearest_node_inside(p[2], P.bmin[2], P.scale[2]);
-        } else {
-            inside = in_range & (p[0] >= P.bmin[0]) & (p[0] <= P.bmax[0]) & (p[1] >= P.bmin[1])
-                     & (p[1] <= P.bmax[1]) & (p[2] >= P.bmin[2]) & (p[2] <= P.bmax[2]);
-            // node indices are clamped to the grid for any position; they
-            // are used only for samples inside the box
-            ix = nearest_node(p[0], P.bmin[0], P.scale[0], hi_node);
-            iy = nearest_node(p[1], P.bmin[1], P.scale[1], hi_node);
-            iz = nearest_node(p[2], P.bmin[2], P.scale[2], hi_node);
-        }
+        // the sample lands
+        const float t_i = t;
+        const uint32_t jx = ix, jy = iy, jz = iz;
+        const bool inside_i = inside;
         float sigma = 0.0f;
         int32_t leap = 0;
         if (inside) {
@@ -1084,21 +1221,20 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
             // sigma = 0 without reading the planes
             bool dead = false;
             if constexpr (LIN && SKIP) {
-                const uint32_t cc[3] = {ix >> P.cell_shift, iy >> P.cell_shift, iz >> P.cell_shift};
-                const uint32_t cd = P.cell_dist[(cc[0] * P.cell_m + cc[1]) * P.cell_m + cc[2]];
-                if (cd != 0) {
+                if (cell != 0) {
                     dead = true;
-                    leap = leap_cells(P, cd, cc, g0, inv_ds, leap_margin, i);
+                    const uint32_t cc[3] = {ix >> P.cell_shift, iy >> P.cell_shift, iz >> P.cell_shift};
+                    leap = leap_cells(P, cell, cc, g0, inv_ds, leap_margin, i);
+                } else {
+                    gather_planes();
                 }
             }
             if (!dead) {
                 float sxy, syz, szx;
                 uint32_t dxy, dyz, dzx;
-                constexpr uint32_t RB = SigmaRecord<ST>::bytes;
-                const uint32_t bnm1 = RB * static_cast<uint32_t>(n_p - 1);
-                SigmaRecord<ST>::load(P.sigma[0], record_offset<RB>(row_part<RB>(ix, bnm1), iy), sxy, dxy);
-                SigmaRecord<ST>::load(P.sigma[1], record_offset<RB>(row_part<RB>(iy, bnm1), iz), syz, dyz);
-                SigmaRecord<ST>::load(P.sigma[2], record_offset<RB>(row_part<RB>(iz, bnm1), ix), szx, dzx);
+                Rec::unpack(raw[0], sxy, dxy);
+                Rec::unpack(raw[1], syz, dyz);
+                Rec::unpack(raw[2], szx, dzx);
                 if constexpr (LIN) {
                     // Eq. 5 on the folded per-plane partial sums
                     float pre = sxy + syz;
@@ -1121,51 +1257,46 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
                 }
             }
         }
-        // in-box samples among first .. last-1 (diagnostics of a leap)
-        auto count_inbox = [&](int32_t first, int32_t last) {
-            uint32_t n = 0;
-            for (int32_t k = first; k < last; ++k) {
-                const float tk = sample_t(P, stratified, ray_key, k);
-                bool in_k = true;
-#pragma unroll
-                for (int r = 0; r < 3; ++r) {
-                    const float pk = o[r] + tk * d[r];
-                    in_k = in_k & (pk >= P.bmin[r]) & (pk <= P.bmax[r]);
-                }
-                n += in_k ? 1u : 0u;
-            }
-            return n;
+        // the next sample: past the furthest of the empty runs [i, leap) that
+        // the ray's lanes found (each is a valid leap: the sample has
+        // sigma^j = 0 in the plane with distance dmax, the rest stay within
+        // its empty square), or the next chunk
+        int32_t next = base + L;
+        auto leap_on = [&]() {
+            if constexpr (SKIP && L == 1)
+                next = leap != 0 ? leap : next;
+            else if constexpr (SKIP)
+                next = max(next, grp_max<L>(leap));
         };
-        bool leapt = false;
-        if constexpr (SKIP && L == 1) {
-            if (leap != 0) {
-                // samples i .. leap-1 are empty: sample i has sigma^j = 0 in
-                // the plane with distance dmax, the rest stay within its
-                // empty square
-                if constexpr (STATS)
-                    n_inbox += count_inbox(i, leap);
-                base = leap;
-                t = sample_t(P, stratified, ray_key, base);
-                leapt = true;
-            }
+        float t_chunk;             // t of this lane's sample in the next chunk
+        if constexpr (kAhead) {
+            leap_on();
+            t = sample_t(P, stratified, ray_key, next + s);
+            t_chunk = t;
+        } else {
+            t_chunk = sample_t(P, stratified, ray_key, base + L + s);
         }
-        if (!leapt) {
         float q = 0.0f;
         uint64_t excl = 0, total = 0;
         // a chunk in which no lane of the wave is occupied adds nothing to
         // the optical depth: the exchange of t and the scan are skipped (a
         // wave-uniform branch, so every group is whole inside it)
-        if (L == 1 || __builtin_amdgcn_ballot_w64(sigma > 0.0f) != 0) {
+        if (__builtin_amdgcn_ballot_w64(sigma > 0.0f) != 0) {
             // t_{i+1}: the next lane's t, or for the group's last lane the
-            // first sample of the next chunk
-            const float t_first_next = grp_first<L>(t_next_chunk);
-            const float t_lane_next = grp_next<L>(t);
+            // first sample of the next chunk, which is where the march goes
+            // on unless it leaps
+            if constexpr (kAhead && SKIP && L > 1) {
+                if (next != base + L)
+                    t_chunk = sample_t(P, stratified, ray_key, base + L + s);
+            }
+            const float t_first_next = grp_first<L>(t_chunk);
+            const float t_lane_next = grp_next<L>(t_i);
             float tn = (s == L - 1) ? t_first_next : t_lane_next;
             if (i + 1 >= N)
                 tn = P.far_t;
             uint64_t Q = 0;
             if (sigma > 0.0f) {
-                const float gap = fmaxf(0.0f, tn - t);
+                const float gap = fmaxf(0.0f, tn - t_i);
                 const float delta = gap * dn;
                 q = sigma * delta;
                 Q = fixed_q(q);
@@ -1173,91 +1304,89 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
             grp_scan<L>(Q, s, excl, total);
         }
         const uint64_t tau_i = tau + excl;
-        // with one lane per ray the loop condition already guarantees
-        // tau_i = tau <= tau_eps and i <= i1
-        const bool live = (L == 1) || (in_range & (tau_i <= static_cast<uint64_t>(P.tau_eps)));
-        const bool occ = live & (sigma > 0.0f);
-        // queue positions of this step's occupied samples, in lane order
-        const uint64_t occ_mask = kDefer ? __builtin_amdgcn_ballot_w64(occ) : 0;
-        if (occ && !kDefer) {
-            float col[3];
-            if constexpr (LIN)
-                sample_colour_lin<UT, DC>(P, __umul24(ix, n_p) + iy, __umul24(iy, n_p) + iz,
-                                          __umul24(iz, n_p) + ix, lin, col);
-            else
-                sample_colour<UT, DC, BS>(P, __umul24(ix, n_p) + iy, __umul24(iy, n_p) + iz,
-                                          __umul24(iz, n_p) + ix, beta, col);
-            const float T = transmittance(tau_i);
-            const float alpha = -expm1f(-q);
-            const double w = static_cast<double>(T * alpha);
-            acc_r = fma(w, static_cast<double>(col[0]), acc_r);
-            acc_g = fma(w, static_cast<double>(col[1]), acc_g);
-            acc_b = fma(w, static_cast<double>(col[2]), acc_b);
-            acc_t = fma(w, static_cast<double>(t), acc_t);
-        }
-        if (occ && kDefer) {
-            const float T = transmittance(tau_i);
-            const float alpha = -expm1f(-q);
-            const float w = T * alpha;
-            acc_t = fma(static_cast<double>(w), static_cast<double>(t), acc_t);
-            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(occ_mask >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(occ_mask), 0u));
-            cq.entries[(q_head + q_count + rank) & (kQueue - 1)] =
-                make_uint4((__umul24(ix, n_p) + iy) | (static_cast<uint32_t>(slot) << 26), __umul24(iy, n_p) + iz,
-                           __umul24(iz, n_p) + ix, __float_as_uint(w));
-            pushed = true;
-        }
-        if (L > 1 && live)
-            last_live = i;
-        if constexpr (STATS) {
-            n_inbox += (live & inside) ? 1u : 0u;
-            n_occ += occ ? 1u : 0u;
-            // FNV-1a over the occupied samples of the group in sample order
-#pragma unroll
-            for (int k = 0; k < L; ++k) {
-                const int src = (lane & ~(L - 1)) + k;
-                const bool o_k = __shfl(occ ? 1 : 0, src) != 0;
-                const uint32_t i_k = static_cast<uint32_t>(__shfl(i, src));
-                const uint32_t x_k = static_cast<uint32_t>(__shfl(static_cast<int>(ix), src));
-                const uint32_t y_k = static_cast<uint32_t>(__shfl(static_cast<int>(iy), src));
-                const uint32_t z_k = static_cast<uint32_t>(__shfl(static_cast<int>(iz), src));
-                if (o_k) {
-                    hash = fnv1a_word(hash, i_k);
-                    hash = fnv1a_word(hash, x_k);
-                    hash = fnv1a_word(hash, y_k);
-                    hash = fnv1a_word(hash, z_k);
-                }
-            }
-        }
         tau += total;
-        int32_t next = base + L;
-        if constexpr (SKIP && L > 1) {
-            // every lane's empty run [i, leap) is a valid leap: the next chunk
-            // starts at the furthest one that ends past this chunk
-            const int32_t last_leap = grp_max<L>(leap);
-            if (last_leap > next && tau <= static_cast<uint64_t>(P.tau_eps)) {
-                if constexpr (STATS) {
-                    if (s == 0)
-                        n_inbox += count_inbox(next, last_leap);
+        // its gathers, unless the ray ends here
+        if constexpr (kAhead) {
+            if (next <= i1 && tau <= static_cast<uint64_t>(P.tau_eps))
+                fetch(next + s);
+        }
+        {
+            // with one lane per ray the loop condition already guarantees
+            // tau_i = tau <= tau_eps and i <= i1
+            const bool live = (L == 1) || ((i <= i1) & (tau_i <= static_cast<uint64_t>(P.tau_eps)));
+            const bool occ = live & (sigma > 0.0f);
+            // queue positions of this step's occupied samples, in lane order
+            const uint64_t occ_mask = kDefer ? __builtin_amdgcn_ballot_w64(occ) : 0;
+            if (occ) {
+                const uint32_t texel0 = __umul24(jx, n_p) + jy, texel1 = __umul24(jy, n_p) + jz;
+                const uint32_t texel2 = __umul24(jz, n_p) + jx;
+                const float T = transmittance(tau_i);
+                const float w = T * opacity(q);
+                acc_t = fma(static_cast<double>(w), static_cast<double>(t_i), acc_t);
+                if constexpr (kDefer) {
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                        static_cast<uint32_t>(occ_mask >> 32),
+                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(occ_mask), 0u));
+                    cq.entries[(q_head + q_count + rank) & (kQueue - 1)]
+                        = make_uint4(texel0 | (static_cast<uint32_t>(slot) << 26), texel1, texel2, __float_as_uint(w));
+                    pushed = true;
+                } else {
+                    float col[3];
+                    if constexpr (LIN)
+                        sample_colour_lin<UT, DC>(P, texel0, texel1, texel2, lin, col);
+                    else
+                        sample_colour<UT, DC, BS>(P, texel0, texel1, texel2, beta, col);
+                    const double wd = static_cast<double>(w);
+                    acc_r = fma(wd, static_cast<double>(col[0]), acc_r);
+                    acc_g = fma(wd, static_cast<double>(col[1]), acc_g);
+                    acc_b = fma(wd, static_cast<double>(col[2]), acc_b);
                 }
-                next = last_leap;
+            }
+            if (L > 1 && live)
+                last_live = i;
+            if constexpr (STATS) {
+                n_inbox += (live & inside_i) ? 1u : 0u;
+                n_occ += occ ? 1u : 0u;
+                // FNV-1a over the occupied samples of the group in sample order
+#pragma unroll
+                for (int k = 0; k < L; ++k) {
+                    const int src = (lane & ~(L - 1)) + k;
+                    const bool o_k = __shfl(occ ? 1 : 0, src) != 0;
+                    const uint32_t i_k = static_cast<uint32_t>(__shfl(i, src));
+                    const uint32_t x_k = static_cast<uint32_t>(__shfl(static_cast<int>(jx), src));
+                    const uint32_t y_k = static_cast<uint32_t>(__shfl(static_cast<int>(jy), src));
+                    const uint32_t z_k = static_cast<uint32_t>(__shfl(static_cast<int>(jz), src));
+                    if (o_k) {
+                        hash = fnv1a_word(hash, i_k);
+                        hash = fnv1a_word(hash, x_k);
+                        hash = fnv1a_word(hash, y_k);
+                        hash = fnv1a_word(hash, z_k);
+                    }
+                }
             }
         }
-        t = (next == base + L) ? t_next_chunk : sample_t(P, stratified, ray_key, next + s);
+        if constexpr (!kAhead) {
+            leap_on();
+            t = next == base + L ? t_chunk : sample_t(P, stratified, ray_key, next + s);
+        }
+        if constexpr (STATS && SKIP) {
+            // the samples a leap passes over, past the chunk
+            if (next > base + L && s == 0 && tau <= static_cast<uint64_t>(P.tau_eps))
+                n_inbox += count_inbox(base + L, next);
+        }
         base = next;
-        }   // !leapt
         }   // active
         if constexpr (kDefer) {
             // whole wave: count the pushes; evaluate 64 once they are waiting
             q_count += static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(pushed)));
             if (q_count >= 64) {
-                drain_colour<UT, DC, LIN, BS, (L > 1 || DC == 16)>(P, cq, q_head, 64);
+                drain_colour<UT, DC, LIN, BS, kQuads>(P, cq, q_head, 64);
                 q_count -= 64;
             }
         }
     }
     if constexpr (kDefer)
-        drain_colour<UT, DC, LIN, BS, (L > 1 || DC == 16)>(P, cq, q_head, q_count);
+        drain_colour<UT, DC, LIN, BS, kQuads>(P, cq, q_head, q_count);
 
     // combine the lanes of the ray
     if constexpr (!kDefer) {
@@ -1301,7 +1430,7 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
     }
 }
 
-// Launch shapes: L = 1, 4 or 8 lanes per ray over workgroup tiles of
+// Launch shapes: L = 1, 2, 4 or 8 lanes per ray over workgroup tiles of
 // kTileW(L) x kTileH(L) pixels, with or without leaps over empty space.
 // LDS floats of the folded Eq. 5 weights per workgroup (64 rays); a run-time
 // D also keeps beta after the rows.
@@ -1311,12 +1440,16 @@ constexpr int lin_smem_floats()
     return LIN ? (DC > 0 ? lin_stride(DC) : lin_stride_generic(32)) * (kBlockThreads / 4) : 4;
 }
 
-// LDS floats of beta per workgroup: one copy per lane with one lane per
-// ray, one per ray (64) with four; Eq. 5 keeps it in the folded rows.
+// Rays of a workgroup with L > 1 lanes per ray, at least 64 (the stride of
+// beta's components in LDS).
+constexpr int rays_stride(int L) { return L == 2 ? 128 : 64; }
+
+// LDS floats of beta per workgroup: one copy per ray; Eq. 5 keeps it in the
+// folded rows.
 template <int DC, bool LIN, int L = 1>
 constexpr int beta_smem_floats()
 {
-    return LIN ? 4 : (DC > 0 ? DC : 32) * (L == 4 ? 64 : kBlockThreads);
+    return LIN ? 4 : (DC > 0 ? DC : 32) * (L == 1 ? kBlockThreads : rays_stride(L));
 }
 
 // Waves per SIMD: the register target, capped by how many 4-wave workgroups
@@ -1332,12 +1465,28 @@ constexpr int occupancy()
     // measured 3-4% faster at seven waves than at eight: one wave less for
     // both.
     constexpr int rec0 = waves_per_simd(3 * DC * static_cast<int>(sizeof(UT)));
-    constexpr int rec = (NDC || (L >= 4 && !LIN)) && rec0 > 4 ? rec0 - 1 : rec0;
+    constexpr int rec = (NDC || (L >= 2 && !LIN)) && rec0 > 4 ? rec0 - 1 : rec0;
     constexpr int regs = LIN && rec > 6 ? 6 : rec;
     constexpr int lds = 4 * (lin_smem_floats<DC, LIN>() + beta_smem_floats<DC, LIN>())
                         + (defers_colour(DC, LIN) ? 4 * static_cast<int>(kQueue) * 16 + 4 * (64 / L) * 3 * 8 : 0);
     constexpr int by_lds = 163840 / lds;
     return regs < by_lds ? regs : (by_lds < 1 ? 1 : by_lds);
+}
+
+// Pixel of ray slot `slot` in a wave's tile.  One lane per ray: Z order, so
+// that the four lanes of a quad are a block of 2 x 2 pixels, whose texels fall
+// in fewer 64-byte segments than those of four pixels in a row (a gather costs
+// the memory pipeline by the segments its quads touch): 1% on a batch of views.  With more lanes a quad
+// holds samples of one ray, and the tile is in row order.
+template <int L>
+__device__ __forceinline__ int32_t slot_x(int32_t slot)
+{
+    return L == 1 ? (slot & 1) | ((slot >> 1) & 2) | ((slot >> 2) & 4) : slot % kWaveW(L);
+}
+template <int L>
+__device__ __forceinline__ int32_t slot_y(int32_t slot)
+{
+    return L == 1 ? ((slot >> 1) & 1) | ((slot >> 2) & 2) | ((slot >> 3) & 4) : slot / kWaveW(L);
 }
 
 // One workgroup's rays at tile (tx, ty) of view `view`, with the LDS arrays
@@ -1346,38 +1495,43 @@ constexpr int occupancy()
 template <typename ST, typename UT, int DC, bool STATS, int L, bool SKIP, bool LIN, bool NDC>
 __device__ __forceinline__ void workgroup_rays(const RenderParams& P, int32_t view, int32_t tx, int32_t ty,
                                                float* beta_smem, float* lin_smem, uint4* queue_smem,
-                                               double* qacc_smem, RayGeom* geom)
+                                               double* qacc_smem, RayLds<NDC>* geom)
 {
     const int32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int32_t WW = kWaveW(L), WH = kWaveH(L);
     const int32_t slot = lane / L;
-    const int32_t u = tx * kTileW(L) + (wave & 1) * WW + (slot % WW);
-    const int32_t v = ty * kTileH(L) + (wave >> 1) * WH + (slot / WW);
-    if constexpr (L >= 4) {
-        // Four or eight lanes per ray: the first wave computes beta and the
-        // second the march geometry of the workgroup's 256 / L rays, one lane
-        // per ray, and the four waves march from them; the ray setup then
-        // costs one wave's instructions per workgroup instead of L (the
-        // march is bound by vector-ALU issue).  Eq. 5 (four lanes) keeps
-        // beta in the ray's row of folded weights, which its lanes fold.
+    const int32_t u = tx * kTileW(L) + (wave & 1) * WW + slot_x<L>(slot);
+    const int32_t v = ty * kTileH(L) + (wave >> 1) * WH + slot_y<L>(slot);
+    if constexpr (L >= 2) {
+        // More lanes per ray: the first waves compute beta and the next ones
+        // the march geometry of the workgroup's 256 / L rays (one wave each;
+        // two with two lanes), one lane per ray, and the four waves march
+        // from them; the ray setup then costs one wave's instructions per
+        // 64 rays instead of L (the march is bound by vector-ALU issue).
+        // Eq. 5 (four lanes) keeps beta in the ray's row of folded weights,
+        // which its lanes fold.
         constexpr int32_t stride = LIN && DC > 0 ? lin_stride(DC) : 0;
         auto lin_row = [&](int32_t r) { return lin_smem + r * (DC > 0 ? stride : P.lin_stride); };
         constexpr int32_t RPW = 64 / L;   // rays per wave
-        if (wave < 2 && lane < 4 * RPW) {
-            const int32_t w = lane / RPW, sl = lane % RPW;
-            const int32_t ur = tx * kTileW(L) + (w & 1) * WW + (sl % WW);
-            const int32_t vr = ty * kTileH(L) + (w >> 1) * WH + (sl / WW);
+        constexpr int32_t kSetup = L == 2 ? 2 : 1;   // waves per role
+        constexpr int32_t RS = rays_stride(L);
+        const int32_t sr = (wave % kSetup) * 64 + lane;
+        if (wave < 2 * kSetup && sr < 4 * RPW) {
+            const int32_t w = sr / RPW, sl = sr % RPW;
+            const int32_t ur = tx * kTileW(L) + (w & 1) * WW + slot_x<L>(sl);
+            const int32_t vr = ty * kTileH(L) + (w >> 1) * WH + slot_y<L>(sl);
             if (view < P.n_views && ur < P.width && vr < P.height) {
                 float o_w[3], d_w[3];
                 pixel_ray(P, view, ur, vr, o_w, d_w);
-                // wave 0: beta, wave 1: the march geometry
-                if (wave == 0) {
+                if (wave < kSetup) {
                     if constexpr (LIN)
-                        lookup_beta<DC, 1>(P, d_w, DC > 0 ? lin_row(lane) : lin_row(lane) + 9 * P.D + 3);
+                        lookup_beta<DC, 1>(P, d_w, DC > 0 ? lin_row(sr) : lin_row(sr) + 9 * P.D + 3);
                     else
-                        lookup_beta<DC, 64>(P, d_w, beta_smem + lane);
+                        lookup_beta<DC, RS>(P, d_w, beta_smem + sr);
                 } else {
-                    march_geometry<SKIP, NDC>(P, o_w, d_w, geom[lane]);
+                    RayGeom g;
+                    march_geometry<SKIP, NDC>(P, o_w, d_w, g);
+                    geom[sr].put(g);
                 }
             }
         }
@@ -1388,7 +1542,7 @@ __device__ __forceinline__ void workgroup_rays(const RenderParams& P, int32_t vi
         cq.acc = qacc_smem + wave * RPW * 3;
         cq.beta = beta_smem + wave * RPW;
         if (view < P.n_views && u < P.width && v < P.height)
-            render_ray<ST, UT, DC, STATS, L, SKIP, LIN, NDC, true, 64>(P, view, u, v, lane, beta_smem + r,
+            render_ray<ST, UT, DC, STATS, L, SKIP, LIN, NDC, true, RS>(P, view, u, v, lane, beta_smem + r,
                                                                       LIN ? lin_row(r) : nullptr, cq, slot, &geom[r]);
     } else {
         // all lanes of a ray agree on this, so a lane group is never split
@@ -1425,7 +1579,7 @@ __global__ __launch_bounds__(kBlockThreads, (occupancy<UT, DC, LIN, NDC, L>())) 
     constexpr bool kDefer = defers_colour(DC, LIN);
     __shared__ uint4 queue_smem[kDefer ? 4 * kQueue : 1];
     __shared__ double qacc_smem[kDefer ? 4 * (64 / L) * 3 : 1];
-    __shared__ RayGeom geom_smem[L >= 4 ? 64 : 1];
+    __shared__ RayLds<NDC> geom_smem[L >= 2 ? rays_stride(L) : 1];
     int32_t view, tx, ty;
     if (P.block_order) {
         // one view: blocks of 2 x 2 tiles from the centre outwards (the
@@ -1466,7 +1620,7 @@ constexpr int hybrid_lds_bytes()
 {
     constexpr bool defer = defers_colour(DC, false);
     return (defer ? 4 * static_cast<int>(kQueue) * 16 : 16) + (defer ? 4 * (64 / L) * 3 * 8 : 16)
-           + (L >= 4 ? 64 * static_cast<int>(sizeof(RayGeom)) : 0) + 4 * beta_smem_floats<DC, false, L>();
+           + (L >= 2 ? rays_stride(L) * static_cast<int>(sizeof(RayLds<false>)) : 0) + 4 * beta_smem_floats<DC, false, L>();
 }
 
 template <typename UT, int DC>
@@ -1506,8 +1660,8 @@ __global__ __launch_bounds__(kBlockThreads, (hybrid_occupancy<UT, DC>())) void r
         // middle of the rectangle outwards
         constexpr int kAcc = kDefer ? 4 * 16 * 3 * 8 : 16;
         double* acc = reinterpret_cast<double*>(lds + kQ);
-        RayGeom* geom = reinterpret_cast<RayGeom*>(lds + kQ + kAcc);
-        float* beta = reinterpret_cast<float*>(lds + kQ + kAcc + 64 * sizeof(RayGeom));
+        RayLds<false>* geom = reinterpret_cast<RayLds<false>*>(lds + kQ + kAcc);
+        float* beta = reinterpret_cast<float*>(lds + kQ + kAcc + 64 * sizeof(RayLds<false>));
         // consecutive workgroups go to the 8 XCDs in turn: the four of a
         // block are the ones 8 apart, so they share one XCD's L2 (a full
         // group of 8 blocks at a time; the last partial group in order)
@@ -1586,6 +1740,8 @@ hipError_t launch_typed(const RenderParams& p, bool stats, hipStream_t stream)
     if (p.lanes == 1)
         return p.skip ? launch_shape<ST, UT, DC, 1, true, false>(p, stats, stream)
                       : launch_shape<ST, UT, DC, 1, false, false>(p, stats, stream);
+    if (p.lanes == 2)
+        return launch_shape<ST, UT, DC, 2, true, false>(p, stats, stream);
     if (p.lanes == 8)
         return p.skip ? launch_shape<ST, UT, DC, 8, true, false>(p, stats, stream)
                       : launch_shape<ST, UT, DC, 8, false, false>(p, stats, stream);

@@ -42,7 +42,7 @@ struct RenderParams {
     float leap_k, leap_c;     // leap index fma(t_exit, leap_k, -leap_c): leap_k = (1 - 2^-19) / dt,
                               // leap_c = near leap_k + 2^-19 |near| / dt (binary64, rounded once)
     // launch geometry
-    int32_t lanes;            // lanes per ray: 1, 4 or 8
+    int32_t lanes;            // lanes per ray: 1, 2, 4 or 8
     int32_t skip;             // 1: one lane per ray with empty-space leaps
     float leap_margin;        // texels a leap keeps from its square's edge
     int32_t tiles_x, tiles_y; // workgroup tiles per view
@@ -171,7 +171,7 @@ hipError_t launch_generate(const GenParams& p, _Float16* enc_table, hipStream_t 
 
 // Workgroup geometry: 256 threads = 4 wave64; with L lanes per ray a wave
 // holds 64/L rays laid out as a wave tile of kWaveW(L) x kWaveH(L) pixels
-// (8x8, 4x4 or 4x2 for L = 1, 4, 8) and a workgroup covers 2 x 2 wave tiles.
+// (8x8, 8x4, 4x4 or 4x2 for L = 1, 2, 4, 8) and a workgroup covers 2 x 2 wave tiles.
 constexpr int kBlockThreads = 256;
 constexpr int kWaveW(int L) { return L >= 4 ? 4 : 8; }
 constexpr int kWaveH(int L) { return (64 / L) / kWaveW(L); }
