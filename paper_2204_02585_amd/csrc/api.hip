@@ -21,6 +21,7 @@ struct sqn_caches {
     const void* sigma[3];
     const void* uvw[3];
     const void* beta;
+    int32_t D;               // components of the stored records, desc.D or more
     float scale[3];          // (n_p - 1) / (bmax - bmin), binary32
     int64_t tau_eps;         // floor(-ln(eps) 2^32)
     int32_t lanes;           // lanes per ray, 0 = chosen per call
@@ -276,13 +277,13 @@ sqn_status render_common(const sqn_caches* h, const float* poses, int32_t n_pose
         p.scale[r] = h->scale[r];
     }
     p.n_p = h->desc.n_p;
-    p.D = h->desc.D;
+    p.D = h->D;
     p.n_theta = h->desc.n_theta;
     p.n_phi = h->desc.n_phi;
     p.beta_f16 = h->desc.beta_dtype == SQN_F16;
     p.theta_scale = static_cast<double>(h->desc.n_theta - 1) / 3.14159265358979323846;
     p.phi_scale = static_cast<double>(h->desc.n_phi) / (2.0 * 3.14159265358979323846);
-    p.rec_bytes = static_cast<uint32_t>(3 * h->desc.D * dtype_size(h->desc.uvw_dtype));
+    p.rec_bytes = static_cast<uint32_t>(3 * h->D * dtype_size(h->desc.uvw_dtype));
     p.tau_eps = h->tau_eps;
     p.seed = h->desc.seed;
     p.inv_dt = 1.0f / p.dt;
@@ -301,7 +302,7 @@ sqn_status render_common(const sqn_caches* h, const float* poses, int32_t n_pose
     p.b_sigma = h->b_sigma;
     p.lin_w = h->lin_w;
     // rows per ray in LDS; the kernels for D = 8 and 16 use lin_stride(D)
-    p.lin_stride = sqn::lin_stride_generic(h->desc.D);
+    p.lin_stride = sqn::lin_stride_generic(h->D);
     p.ndc_near = h->ndc_near;
     p.cell_dist = h->cell_dist;
     p.cell_shift = h->cell_shift;
@@ -366,14 +367,30 @@ size_t align256(size_t x) { return (x + 255) & ~size_t{255}; }
 // Where each array of a handle lives in its device block (offsets from the
 // block start, each region 256-byte aligned) and the block size.
 struct CacheLayout {
+    int32_t D;                // components per stored record
     size_t packed_bytes, uvw_bytes, beta_bytes, lin_bytes, cells;
     size_t off_sigma[3], off_uvw[3], off_beta, off_lin, off_cells, total;
 };
 
-CacheLayout cache_layout(const sqn_cache_desc* desc, bool linear)
+// Components per stored record.  The kernels compiled for D = 8 and 16 read a
+// channel as whole 16-byte pieces and defer colour; another D up to 16 runs on
+// them with its records filled up by components of zero, in uvw and beta (they
+// add exactly nothing to a dot product).  617 x 463 x 200 of a 384 cache, D =
+// 12: 0.42 ms on the kernel for any D (one load per component), 0.14 ms filled
+// up to 16; 72-byte records become 96, which counts only where HBM bounds a
+// view.  Any other D, and planes that would pass 2^32 bytes, stay as they are.
+int32_t stored_components(const sqn_cache_desc* desc)
+{
+    const int32_t D = desc->D <= 8 ? 8 : (desc->D <= 16 ? 16 : desc->D);
+    const uint64_t plane = static_cast<uint64_t>(desc->n_p) * desc->n_p * 3u * D * dtype_size(desc->uvw_dtype);
+    const uint64_t beta = static_cast<uint64_t>(desc->n_theta) * desc->n_phi * D * dtype_size(desc->beta_dtype);
+    return plane < (uint64_t{1} << 32) && beta < (uint64_t{1} << 32) ? D : desc->D;
+}
+
+CacheLayout cache_layout(const sqn_cache_desc* desc, bool linear, int32_t D)
 {
     CacheLayout L;
-    const int32_t D = desc->D;
+    L.D = D;
     const size_t texels = static_cast<size_t>(desc->n_p) * desc->n_p;
     // packed records: 4 bytes for binary16 sigma, 8 for binary32 sigma or
     // the linear decoder's binary32 partial sums, four rows interleaved
@@ -479,10 +496,72 @@ __global__ __launch_bounds__(256) void copy_arrays(const CopyArgs A)
     }
 }
 
-// The uvw planes and the direction cache into the handle's block.
-hipError_t copy_uvw_beta(const void* const uvw[3], const void* beta, char* base, const CacheLayout& lay,
-                         hipStream_t stream)
+struct FillArgs {
+    const void* src[4];
+    void* dst[4];
+    uint32_t runs[4];         // runs of D components (three per texel of a plane, one per direction)
+};
+
+// Runs of D components into runs of DS > D (a multiple of 8), zeros after
+// them: array blockIdx.y, one 8-component piece of a run per thread.
+template <typename T>
+__device__ __forceinline__ void fill_piece(const void* src, void* dst, uint32_t run, uint32_t piece, int32_t D,
+                                           int32_t DS)
 {
+    const T* in = static_cast<const T*>(src) + static_cast<size_t>(run) * D;
+    T v[8];
+#pragma unroll
+    for (int32_t e = 0; e < 8; ++e) {
+        const int32_t k = 8 * static_cast<int32_t>(piece) + e;
+        v[e] = in[k < D ? k : D - 1];
+        v[e] = k < D ? v[e] : T{0};
+    }
+    uint4* out = reinterpret_cast<uint4*>(static_cast<T*>(dst) + static_cast<size_t>(run) * DS + 8 * piece);
+    uint4 q[sizeof(v) / 16];
+    __builtin_memcpy(q, v, sizeof(v));
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(v) / 16; ++k)
+        out[k] = q[k];
+}
+
+__global__ __launch_bounds__(256) void fill_arrays(const FillArgs A, int32_t D, int32_t DS, int32_t uvw16,
+                                                   int32_t beta16)
+{
+    const int32_t y = blockIdx.y;
+    const void* src = y == 0 ? A.src[0] : (y == 1 ? A.src[1] : (y == 2 ? A.src[2] : A.src[3]));
+    void* dst = y == 0 ? A.dst[0] : (y == 1 ? A.dst[1] : (y == 2 ? A.dst[2] : A.dst[3]));
+    const uint32_t runs = y == 0 ? A.runs[0] : (y == 1 ? A.runs[1] : (y == 2 ? A.runs[2] : A.runs[3]));
+    const uint32_t pieces = static_cast<uint32_t>(DS) / 8;
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t run = i / pieces;
+    if (run >= runs)
+        return;
+    if (y < 3 ? uvw16 : beta16)
+        fill_piece<uint16_t>(src, dst, run, i - run * pieces, D, DS);
+    else
+        fill_piece<uint32_t>(src, dst, run, i - run * pieces, D, DS);
+}
+
+// The uvw planes and the direction cache into the handle's block.
+hipError_t copy_uvw_beta(const sqn_cache_desc* desc, const void* const uvw[3], const void* beta, char* base,
+                         const CacheLayout& lay, hipStream_t stream)
+{
+    if (lay.D != desc->D) {
+        FillArgs f;
+        uint32_t most = 0;
+        for (int k = 0; k < 4; ++k) {
+            f.src[k] = k < 3 ? uvw[k] : beta;
+            f.dst[k] = base + (k < 3 ? lay.off_uvw[k] : lay.off_beta);
+            // at most 3 * 8192^2 or 2^31 / D runs of at most two pieces
+            f.runs[k] = k < 3 ? 3u * static_cast<uint32_t>(desc->n_p) * static_cast<uint32_t>(desc->n_p)
+                              : static_cast<uint32_t>(desc->n_theta) * static_cast<uint32_t>(desc->n_phi);
+            most = f.runs[k] > most ? f.runs[k] : most;
+        }
+        const uint64_t threads = static_cast<uint64_t>(most) * static_cast<uint32_t>(lay.D / 8);
+        fill_arrays<<<dim3(static_cast<uint32_t>((threads + 255) / 256), 4), 256, 0, stream>>>(
+            f, desc->D, lay.D, desc->uvw_dtype == SQN_F16, desc->beta_dtype == SQN_F16);
+        return hipGetLastError();
+    }
     const void* const src[4] = {uvw[0], uvw[1], uvw[2], beta};
     char* const dst[4] = {base + lay.off_uvw[0], base + lay.off_uvw[1], base + lay.off_uvw[2], base + lay.off_beta};
     const size_t bytes[4] = {lay.uvw_bytes, lay.uvw_bytes, lay.uvw_bytes, lay.beta_bytes};
@@ -530,12 +609,12 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     if (!sigma_planes || !uvw_planes)
         return fail(SQN_ERR_INVALID_ARG, "plane pointer array is NULL");
 
-    const int32_t D = desc->D;
     const int32_t ds = linear ? dec->d_sigma : 1;
     const size_t texels = static_cast<size_t>(desc->n_p) * desc->n_p;
     const size_t sigma_bytes = texels * ds * dtype_size(desc->sigma_dtype);
-    const CacheLayout lay = cache_layout(desc, linear);
-    const size_t uvw_bytes = lay.uvw_bytes, beta_bytes = lay.beta_bytes, lin_bytes = lay.lin_bytes;
+    const CacheLayout lay = cache_layout(desc, linear, stored_components(desc));
+    const int32_t D = lay.D, Du = desc->D;   // stored, and the caller's
+    const size_t uvw_bytes = lay.uvw_bytes / D * Du, beta_bytes = lay.beta_bytes / D * Du, lin_bytes = lay.lin_bytes;
     const size_t lin_rows = 9 * static_cast<size_t>(D) + 3;
     const int32_t cell_shift = sqn::linear_cell_shift(desc->n_p);
     const int32_t cell_m = sqn::linear_cells(desc->n_p);
@@ -560,14 +639,16 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     std::vector<float> lin_host;
     if (linear) {
         lin_host.resize(lin_rows * D);
+        // (zeros at the components the records are filled up with)
         for (int32_t c = 0; c < 3; ++c)
-            for (int32_t e = 0; e < 3 * D; ++e)
-                for (int32_t d = 0; d < D; ++d)
-                    lin_host[(static_cast<size_t>(c) * 3 * D + e) * D + d]
-                        = dec->w_uvw[(static_cast<size_t>(c) * D + d) * 3 * D + e];
+            for (int32_t j = 0; j < 3; ++j)
+                for (int32_t e = 0; e < Du; ++e)
+                    for (int32_t d = 0; d < Du; ++d)
+                        lin_host[(static_cast<size_t>(c) * 3 * D + j * D + e) * D + d]
+                            = dec->w_uvw[(static_cast<size_t>(c) * Du + d) * 3 * Du + j * Du + e];
         for (int32_t c = 0; c < 3; ++c)
-            for (int32_t d = 0; d < D; ++d)
-                lin_host[(9 * static_cast<size_t>(D) + c) * D + d] = dec->b_uvw[c * D + d];
+            for (int32_t d = 0; d < Du; ++d)
+                lin_host[(9 * static_cast<size_t>(D) + c) * D + d] = dec->b_uvw[c * Du + d];
     }
 
     sqn_caches* h = static_cast<sqn_caches*>(calloc(1, sizeof(sqn_caches)));
@@ -624,7 +705,7 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
         e = sqn::prepare_sigma_planes(sigma_planes, desc->sigma_dtype, desc->n_p, packed, pw, st);
     }
     if (e == hipSuccess)
-        e = copy_uvw_beta(uvw_planes, beta, base, lay, st);
+        e = copy_uvw_beta(desc, uvw_planes, beta, base, lay, st);
     if (e == hipSuccess)
         e = hipStreamSynchronize(st);
     else
@@ -639,6 +720,7 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     }
     for (int r = 0; r < 3; ++r)
         h->scale[r] = static_cast<float>(desc->n_p - 1) / (desc->bbox_max[r] - desc->bbox_min[r]);
+    h->D = D;
     h->tau_eps = tau_threshold(desc->t_eps);
     h->skip = 1;
     if (linear) {
@@ -795,7 +877,10 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
         return fail(SQN_ERR_DEVICE, "hipGetDevice failed");
     if (device != caches->device)
         return fail(SQN_ERR_INVALID_ARG, "caches live on device %d, current device is %d", caches->device, device);
-    const CacheLayout lay = cache_layout(desc, false);
+    // records filled up where the block has room for them
+    CacheLayout lay = cache_layout(desc, false, stored_components(desc));
+    if (lay.total > caches->bytes)
+        lay = cache_layout(desc, false, desc->D);
     if (lay.total > caches->bytes)
         return fail(SQN_ERR_INVALID_ARG, "the caches need %zu bytes of device memory, the handle holds %zu",
                     lay.total, caches->bytes);
@@ -806,10 +891,10 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     for (int j = 0; j < 3; ++j) {
         if ((s = check_device_range(sigma_planes[j], sigma_bytes, names_s[j])) != SQN_OK)
             return s;
-        if ((s = check_device_range(uvw_planes[j], lay.uvw_bytes, names_u[j])) != SQN_OK)
+        if ((s = check_device_range(uvw_planes[j], lay.uvw_bytes / lay.D * desc->D, names_u[j])) != SQN_OK)
             return s;
     }
-    if ((s = check_device_range(beta, lay.beta_bytes, "beta")) != SQN_OK)
+    if ((s = check_device_range(beta, lay.beta_bytes / lay.D * desc->D, "beta")) != SQN_OK)
         return s;
 
     // the scratch lies where the uvw planes and the direction cache go; every
@@ -823,7 +908,7 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     void* const packed[3] = {base + lay.off_sigma[0], base + lay.off_sigma[1], base + lay.off_sigma[2]};
     hipError_t e = sqn::prepare_sigma_planes(sigma_planes, desc->sigma_dtype, desc->n_p, packed, pw, st);
     if (e == hipSuccess)
-        e = copy_uvw_beta(uvw_planes, beta, base, lay, st);
+        e = copy_uvw_beta(desc, uvw_planes, beta, base, lay, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SQN_ERR_DEVICE, "cache preparation failed (the handle's contents are now unspecified): %s",
@@ -831,6 +916,7 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     }
     // later renders with the handle read the new arrays
     caches->desc = *desc;
+    caches->D = lay.D;
     for (int j = 0; j < 3; ++j) {
         caches->sigma[j] = base + lay.off_sigma[j];
         caches->uvw[j] = base + lay.off_uvw[j];
