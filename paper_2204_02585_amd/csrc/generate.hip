@@ -318,8 +318,9 @@ __device__ __forceinline__ void direction_points(const GenParams& P, int block, 
         const double c = i == 0 ? d[0] : (i == 1 ? d[1] : d[2]);
         if (f < 3)
             return c;
-        const double y = ldexp(c, k);
-        return t < 3 ? sinpi(y) : cospi(y);
+        double sn, cs;
+        sincospi(ldexp(c, k), &sn, &cs);
+        return t < 3 ? sn : cs;
     });
     __syncthreads();
     const GenNet& net = P.dir;
@@ -482,12 +483,13 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(GenParams P, int b
     const double xa = node(ax_a, ia), xb = node(ax_b, ib);
     // NeRF order [a, b, sin a, sin b, cos a, cos b, ...] per frequency
     encode_quarter(P.pos_in, x0, [&](int f) {
-        const int r = f < 2 ? f : f - 2, k = r >> 2, t = r & 3;
-        const double c = (t & 1) ? xb : xa;
+        // sines at f mod 4 = 2, 3, cosines at 0, 1 (f mod 4 is the same in
+        // every lane)
+        const double c = (f & 1) ? xb : xa;
         if (f < 2)
             return c;
-        const double y = ldexp(c, k);
-        return t < 2 ? sinpi(y) : cospi(y);
+        const double y = ldexp(c, (f - 2) >> 2);
+        return (f & 2) ? sinpi(y) : cospi(y);
     });
     __syncthreads();
     const GenNet& net = j == 0 ? P.pos[0] : (j == 1 ? P.pos[1] : P.pos[2]);
@@ -498,11 +500,13 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(GenParams P, int b
 
 }  // namespace
 
-// Grids of at most kSmallBlocks workgroups of 32 points take small_kernel: all
-// of it in one launch, 256 compute units with two workgroups each at a time,
-// every workgroup streaming the 0.85 MB of its network from L2.  Beyond, the
-// pipelined kernel's eight times fewer passes over the weights win.
-constexpr int64_t kSmallBlocks = 1280;
+// Position grids of at most kSmallBlocks workgroups of 32 points (n_p <= 97)
+// take small_kernel: all of it in one launch, every workgroup streaming the
+// 0.85 MB of its network from L2.  Beyond, the pipelined kernel's eight times
+// fewer passes over the weights win.  Small against pipelined kernel, us, with
+// 64 x 64 directions: n_p = 16 25 / 50, 64 27 / 50, 80 38 / 50, 96 49 / 51,
+// 108 58 / 51, 128 73 / 52, 192 147 / 96.
+constexpr int64_t kSmallBlocks = 896;
 
 hipError_t launch_generate(const GenParams& p, _Float16* enc_table, hipStream_t stream)
 {

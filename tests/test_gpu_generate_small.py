@@ -12,9 +12,9 @@ from tests.test_gpu_generate import _full_compare, _generate
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_p,n_theta,n_phi", [(5, 2, 3), (33, 6, 11), (116, 3, 33), (117, 31, 2)])
+@pytest.mark.parametrize("n_p,n_theta,n_phi", [(5, 2, 3), (33, 6, 11), (97, 3, 33), (98, 31, 2)])
 def test_sizes_around_the_rule(n_p, n_theta, n_phi):
-    """3 ceil(n_p^2 / 32) = 1263 at 116 (the small kernel), 1284 at 117."""
+    """3 ceil(n_p^2 / 32) = 885 at 97 (the small kernel), 903 at 98."""
     cfg = dataclasses.replace(scenes.GEN_CONFIGS["gen_tiny"], pos_layers=3, dir_layers=2)
     _full_compare(scenes.make_gen_scene(cfg), f"around {n_p}", n_p=n_p, n_theta=n_theta, n_phi=n_phi)
 
