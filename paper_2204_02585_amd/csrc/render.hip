@@ -27,6 +27,7 @@
 #include <math.h>
 
 #include "atan2_lookup.h"
+#include "opacity.h"
 #include "sqn_internal.h"
 
 namespace sqn {
@@ -603,33 +604,6 @@ __device__ __forceinline__ void sample_colour_lin(const RenderParams& P, uint32_
             col[c] = sigmoid(x);
         }
     }
-}
-
-// 1 - exp(-q) for q >= 0, to about one unit in the last place of the result
-// for small q too: with -q log2(e) = n + f, |f| <= 1/2, it is
-// (1 - 2^n) - 2^n (2^f - 1), and 2^f - 1 = f p(f) by the Taylor series of
-// degree 7 (its next term is below 2^-25 of it).  n = 0, where 1 - 2^n
-// vanishes, is the only case with cancellation in a direct evaluation.  19
-// instructions against about 50 of -expm1f(-q): 1% on the views, whose
-// vector ALUs are near saturation.  NaN stays NaN.
-__device__ __forceinline__ float opacity(float q)
-{
-    const float qc = q > 64.0f ? 64.0f : q;
-    constexpr float kHi = 1.44269502162933349609375f, kLo = 1.92596299112661746887e-8f;   // log2(e)
-    const float n = __builtin_rintf(-qc * kHi);
-    float f = fmaf(-qc, kHi, -n);
-    f = fmaf(-qc, kLo, f);
-    // ln(2)^k / k!
-    float p = 1.52527338040598402800e-5f;
-    p = fmaf(p, f, 1.54035303933816099544e-4f);
-    p = fmaf(p, f, 1.33335581464284434234e-3f);
-    p = fmaf(p, f, 9.61812910762847716198e-3f);
-    p = fmaf(p, f, 5.55041086648215799531e-2f);
-    p = fmaf(p, f, 2.40226506959100712334e-1f);
-    p = fmaf(p, f, 6.93147180559945309417e-1f);
-    const float e = p * f;
-    const float s = __builtin_amdgcn_ldexpf(1.0f, static_cast<int32_t>(n));
-    return fmaf(-s, e, 1.0f - s);
 }
 
 // exp(-tau 2^-32) for a 2^-32 fixed-point optical depth.
