@@ -16,11 +16,11 @@
 // is exact and no activation is shuffled.  Activations are rounded to
 // binary16 after bias and ReLU (binary32); accumulation is binary32.
 //
-// On large grids the weights of each layer of a position network are staged
-// through LDS in chunks of 4 K steps x all M-tiles (32 KiB), shared by the
-// workgroup (8 waves, 256 points); each lane reads its 16-byte fragment with
-// one ds_read_b128.  Small grids and the direction network keep 32 points a
-// workgroup and their activations in LDS instead.
+// On large grids the weights of each layer are staged through LDS in chunks of
+// 4 K steps x all M-tiles (32 KiB at 256 units), shared by the workgroup (8
+// waves, 256 points; 4 waves, 128 nodes for the direction network); each lane
+// reads its 16-byte fragment with one ds_read_b128.  Small grids keep 32 points
+// a workgroup and their activations in LDS instead.
 #include <math.h>
 
 #include "sqn_internal.h"
@@ -43,7 +43,7 @@ __device__ __forceinline__ const _Float16* frag_of(const GenNet& net, int l)
 // the unit held by element e of lane-half h in a K step (see the file head)
 __device__ __forceinline__ int kmap(int h, int e) { return 8 * (e >> 2) + 4 * h + (e & 3); }
 
-// ---- 32 points per workgroup (the direction network, small position grids)
+// ---- 32 points per workgroup (small grids)
 //
 // The eight waves share 32 points: wave m computes output tile m of a layer
 // (one accumulator, the K steps in order, so its values are those of the
@@ -419,6 +419,129 @@ __global__ __launch_bounds__(kPosThreads, 1) void position_kernel(GenParams P, c
     }
 }
 
+// ---- large direction grids ---------------------------------------------------
+//
+// 128 nodes per workgroup of four waves, the weights staged through LDS once
+// for all of them (32 KiB): a quarter of the passes over the weights that
+// workgroups of 32 nodes make, and every wave carries nodes of its own where
+// half the waves above repeat a tile.  The K steps run in the same order, so
+// the values are the same bit for bit.
+
+// Stage chunk c of a layer (fragments [c][m][ss][lane][8], `tiles` M-tiles)
+// into LDS.
+__device__ __forceinline__ void stage_chunk(const _Float16* __restrict__ frag, int tiles, _Float16* wbuf)
+{
+    const int n16 = tiles * kChunkSteps * kFrag / 8;      // 16-byte pieces
+    const uint4* src = reinterpret_cast<const uint4*>(frag);
+    uint4* dst = reinterpret_cast<uint4*>(wbuf);
+    for (int i = threadIdx.x; i < n16; i += blockDim.x)
+        dst[i] = src[i];
+}
+
+// One layer: acc[m] = sum over K steps of W-fragment(m, s) x x[s], for
+// m < tiles (TMAX compile-time bound) and KS K steps.
+template <int TMAX, int KS>
+__device__ __forceinline__ void layer(const _Float16* __restrict__ frag, int tiles, const half8 (&x)[KS],
+                                      float16v (&acc)[TMAX], _Float16* wbuf)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int m = 0; m < TMAX; ++m)
+        acc[m] = float16v{};
+#pragma unroll
+    for (int c = 0; c < KS / kChunkSteps; ++c) {
+        __syncthreads();
+        stage_chunk(frag + static_cast<size_t>(c) * tiles * kChunkSteps * kFrag, tiles, wbuf);
+        __syncthreads();
+#pragma unroll
+        for (int ss = 0; ss < kChunkSteps; ++ss) {
+#pragma unroll
+            for (int m = 0; m < TMAX; ++m) {
+                if (m < tiles) {
+                    const half8 a = *reinterpret_cast<const half8*>(wbuf + ((m * kChunkSteps + ss) * 64 + lane) * 8);
+                    acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, x[c * kChunkSteps + ss], acc[m], 0, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+// bias + ReLU, rounded to binary16: the K-step fragments of the next layer
+template <int T>
+__device__ __forceinline__ void activate(const float16v (&acc)[T], const float* __restrict__ bias,
+                                         half8 (&x)[2 * T])
+{
+    const int h = (threadIdx.x & 63) >> 5;
+#pragma unroll
+    for (int m = 0; m < T; ++m) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 b = *reinterpret_cast<const float4*>(bias + 32 * m + 8 * g + 4 * h);
+            const float bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float v = fmaxf(acc[m][4 * g + q] + bv[q], 0.0f);
+                x[2 * m + (g >> 1)][4 * (g & 1) + q] = static_cast<_Float16>(v);
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void direction_kernel(GenParams P)
+{
+    __shared__ __align__(16) _Float16 wbuf[4 * kChunkSteps * kFrag];
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int64_t n_pts = static_cast<int64_t>(P.n_theta) * P.n_phi;
+    const int64_t p_raw = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * 128 + (threadIdx.x >> 6) * 32
+                          + (lane & 31);
+    const bool valid = p_raw < n_pts;
+    const int64_t p = valid ? p_raw : n_pts - 1;
+    const int a = static_cast<int>(p / P.n_phi), b = static_cast<int>(p - static_cast<int64_t>(a) * P.n_phi);
+    const double th = static_cast<double>(a) * (kPi / static_cast<double>(P.n_theta - 1));
+    const double ph = -kPi + static_cast<double>(b) * (2.0 * kPi / static_cast<double>(P.n_phi));
+    const double d[3] = {sin(th) * cos(ph), sin(th) * sin(ph), cos(th)};
+
+    // NeRF order [d, sin(2^0 pi d), cos(2^0 pi d), ...], 3 components each
+    half8 x0[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int f = 16 * s + kmap(h, e);
+            double v = 0.0;
+            if (f < 3) {
+                v = d[f];
+            } else if (f < P.dir_in) {
+                const int r = f - 3, k = r / 6, t = r % 6;
+                const double y = ldexp(d[t % 3], k);
+                v = t < 3 ? sinpi(y) : cospi(y);
+            }
+            x0[s][e] = static_cast<_Float16>(v);
+        }
+
+    const GenNet& net = P.dir;
+    float16v acc[4];
+    half8 x[8];
+    layer<4, 4>(frag_of(net, 0), 4, x0, acc, wbuf);
+    activate<4>(acc, net.bias[0], x);
+    for (int l = 1; l < net.n_hidden; ++l) {
+        layer<4, 8>(frag_of(net, l), 4, x, acc, wbuf);
+        activate<4>(acc, net.bias[l], x);
+    }
+    layer<4, 8>(frag_of(net, net.n_hidden), 1, x, acc, wbuf);
+    if (!valid)
+        return;
+    const float* hb = net.bias[net.n_hidden];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = 8 * g + 4 * h + q;
+            if (row < P.D)
+                store_value(P.beta_out, static_cast<size_t>(p) * P.D + row, acc[0][4 * g + q] + hb[row], P.beta_f16);
+        }
+}
+
 // Per-axis NeRF encoding tables, binary64 evaluation rounded to binary16:
 // tab[axis][i][0] = x_i, [1 + 2k] = sin(2^k pi x_i), [2 + 2k] = cos(2^k pi x_i)
 // with x_i = lo + i (hi - lo) / (n_p - 1).
@@ -438,9 +561,12 @@ __device__ __forceinline__ void encode_node(const GenParams& P, int axis, int i,
 }
 
 // Before the pipelined kernel: the encoding tables (workgroups below
-// enc_blocks, one node of an axis per thread), and the direction network
-// beside them, which as a launch of 128-node workgroups after it took 25 us
-// (64 x 64 nodes) with most of the chip idle.
+// enc_blocks, kEncNodes nodes of an axis each, one per thread of the first
+// wave: the twenty binary64 sines and cosines of a node are a serial chain, and
+// 512 nodes on one compute unit queue for its one pipeline), and the network
+// of a small direction grid beside them, which as a launch of 128-node
+// workgroups after it took 25 us (64 x 64 nodes) with most of the chip idle.
+constexpr int kEncNodes = 64;
 __global__ __launch_bounds__(kSmallThreads) void encode_and_direction(GenParams P, _Float16* __restrict__ tab,
                                                                       int enc_blocks)
 {
@@ -448,8 +574,8 @@ __global__ __launch_bounds__(kSmallThreads) void encode_and_direction(GenParams 
     __shared__ __align__(16) _Float16 x1[8 * 64 * 8];
     const int wg = blockIdx.x;
     if (wg < enc_blocks) {
-        const int k = wg * kSmallThreads + static_cast<int>(threadIdx.x);
-        if (k < 3 * P.n_p)
+        const int k = wg * kEncNodes + static_cast<int>(threadIdx.x);
+        if (static_cast<int>(threadIdx.x) < kEncNodes && k < 3 * P.n_p)
             encode_node(P, k / P.n_p, k % P.n_p, tab);
         return;
     }
@@ -508,24 +634,43 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(GenParams P, int b
 // 108 58 / 51, 128 73 / 52, 192 147 / 96.
 constexpr int64_t kSmallBlocks = 896;
 
+// Direction grids of at most 49,152 nodes (1,536 workgroups of 32) share the
+// launch of the workgroups of 32; larger ones get a launch of
+// direction_kernel.  Shared / own launch, us, with n_p = 16: 200^2 nodes 28 / 39,
+// 256^2 41 / 39, 512^2 133 / 96; n_p = 64: 200^2 41 / 46, 224^2 47 / 46, 256^2
+// 52 / 46, 512^2 146 / 103, 1024^2 520 / 323; n_p = 128: 200^2 66 / 71, 224^2
+// 75 / 70, 256^2 80 / 71, 1024^2 545 / 346.
+constexpr int64_t kSmallDirections = 49152;
+
 hipError_t launch_generate(const GenParams& p, _Float16* enc_table, hipStream_t stream)
 {
     const int64_t n_pos = static_cast<int64_t>(p.n_p) * p.n_p;
     const int64_t n_dir = static_cast<int64_t>(p.n_theta) * p.n_phi;
     const int64_t small = (n_pos + kSmallPoints - 1) / kSmallPoints;
-    const int64_t dir = (n_dir + kSmallPoints - 1) / kSmallPoints;
+    const bool many = n_dir > kSmallDirections;
+    const int64_t dir = many ? 0 : (n_dir + kSmallPoints - 1) / kSmallPoints;
+    hipError_t e;
     if (3 * small <= kSmallBlocks) {
         small_kernel<<<dim3(static_cast<uint32_t>(3 * small + dir)), kSmallThreads, 0, stream>>>(
             p, static_cast<int>(small));
-        return hipGetLastError();
+        e = hipGetLastError();
+    } else {
+        const int enc = (3 * p.n_p + kEncNodes - 1) / kEncNodes;
+        encode_and_direction<<<dim3(static_cast<uint32_t>(enc + dir)), kSmallThreads, 0, stream>>>(p, enc_table, enc);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+        position_kernel<<<dim3(static_cast<uint32_t>((n_pos + kPosPoints - 1) / kPosPoints), 3), kPosThreads, 0,
+                          stream>>>(p, enc_table);
+        e = hipGetLastError();
     }
-    const int enc = (3 * p.n_p + kSmallThreads - 1) / kSmallThreads;
-    encode_and_direction<<<dim3(static_cast<uint32_t>(enc + dir)), kSmallThreads, 0, stream>>>(p, enc_table, enc);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
+    if (e != hipSuccess || !many)
         return e;
-    position_kernel<<<dim3(static_cast<uint32_t>((n_pos + kPosPoints - 1) / kPosPoints), 3), kPosThreads, 0, stream>>>(
-        p, enc_table);
+    // rows of workgroups: the runtime takes at most 2^32 - 1 work items in one
+    // dimension, and grids of up to 2^31 nodes pass validation
+    const int64_t groups = (n_dir + 127) / 128, row = int64_t{1} << 20;
+    direction_kernel<<<dim3(static_cast<uint32_t>(groups < row ? groups : row),
+                            static_cast<uint32_t>((groups + row - 1) / row)),
+                       256, 0, stream>>>(p);
     return hipGetLastError();
 }
 

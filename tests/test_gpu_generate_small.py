@@ -1,13 +1,14 @@
-"""Both generation kernels around the size where one takes over from the
-other, and the small kernel's remainders: whole grids against the oracle, and
-the two kernels' values at the same nodes bit for bit."""
+"""Both generation kernels around the sizes where one takes over from the
+other, for the position and the direction networks, and their remainders:
+whole grids against the oracle, and the kernels' values at the same nodes
+bit for bit."""
 import dataclasses
 
 import numpy as np
 import pytest
 
 from paper_2204_02585_amd import scenes
-from tests.test_gpu_generate import _full_compare, _generate
+from tests.test_gpu_generate import _check, _full_compare, _generate
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +33,46 @@ def test_both_kernels_give_the_same_bits(D, layers):
         assert np.array_equal(sig_s[j], sig_l[j][::2, ::2])
         assert np.array_equal(uvw_s[j], uvw_l[j][::2, ::2])
     assert np.array_equal(beta_s, beta_l)
+
+
+@pytest.mark.parametrize("n_p", [6, 98])
+@pytest.mark.parametrize("n_theta,n_phi", [(192, 256), (193, 256), (3, 16400)])
+def test_direction_sizes_around_the_rule(n_p, n_theta, n_phi):
+    """49,152 nodes share the launch of the workgroups of 32, more get their
+    own; beside both position kernels."""
+    cfg = dataclasses.replace(scenes.GEN_CONFIGS["gen_tiny"], pos_layers=2, dir_layers=2)
+    _full_compare(scenes.make_gen_scene(cfg), f"directions {n_theta}x{n_phi} beside {n_p}", n_p=n_p, n_theta=n_theta,
+                  n_phi=n_phi)
+
+
+@pytest.mark.parametrize("D,layers", [(8, 4), (32, 1), (1, 16)])
+def test_both_direction_kernels_give_the_same_bits(D, layers):
+    """Node (a, b) of a 97 x 256 grid is node (2a, 2b) of a 193 x 512 one."""
+    cfg = dataclasses.replace(scenes.GEN_CONFIGS["gen_tiny"], D=D, pos_layers=1, dir_layers=layers)
+    g = scenes.make_gen_scene(cfg)
+    small = _generate(g, n_p=4, n_theta=97, n_phi=256)[2]
+    large = _generate(g, n_p=4, n_theta=193, n_phi=512)[2]
+    assert np.array_equal(small, large[::2, ::2])
+
+
+def test_largest_direction_grid():
+    """2^28 nodes: 16 work items per node would be more than a launch takes in
+    one dimension.  Sampled nodes against the oracle, and the last one."""
+    import torch
+    from oracle import cachegen as cg
+    from paper_2204_02585_amd import binding
+    cfg = dataclasses.replace(scenes.GEN_CONFIGS["gen_tiny"], D=1, pos_layers=1, dir_layers=1)
+    g = scenes.make_gen_scene(cfg)
+    n = 16384
+    nets = binding.networks_from_gen_scene(g)
+    try:
+        beta = nets.generate(4, n, n, g.bbox_min, g.bbox_max, torch.float32, torch.float16, torch.float16)[2]
+        rng = np.random.Generator(np.random.PCG64(1))
+        ia = np.concatenate([[0, 0, n - 1, n - 1], rng.integers(0, n, 4000)])
+        ib = np.concatenate([[0, n - 1, 0, n - 1], rng.integers(0, n, 4000)])
+        got = beta[torch.from_numpy(ia).cuda(), torch.from_numpy(ib).cuda()].float().cpu().numpy()
+    finally:
+        nets.close()
+    th, ph = ia * (np.pi / (n - 1)), -np.pi + ib * (2.0 * np.pi / n)
+    d = np.stack([np.sin(th) * np.cos(ph), np.sin(th) * np.sin(ph), np.cos(th)], axis=-1)
+    _check(got, cg.mlp(cg.encode(d, cfg.dir_freq), g.dir), "2^28 directions")
