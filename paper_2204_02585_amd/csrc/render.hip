@@ -1447,6 +1447,22 @@ constexpr int occupancy()
     return regs < by_lds ? regs : (by_lds < 1 ? 1 : by_lds);
 }
 
+// Most waves per SIMD the compiler plans registers for.  Eight lanes serve
+// views that do not fill the chip, where the latency of a chain counts and not
+// the waves in flight.  Left alone the compiler plans for the eight waves that
+// their LDS allows, and to stay within 64 registers it issues a drain's
+// gathers in pairs with a wait after each: three round trips to memory instead
+// of one.  160x100x192 of a 384 cache, us, planned for eight waves / as here:
+// D = 8 with binary32 uvw 32.5 / 24.3, D = 16 with binary16 uvw 37.2 / 29.1, any
+// D (24) 264-306 / 153-179; D = 8 with binary16 uvw, whose gathers fit, 23.0 / 22.8.
+// D = 16 with binary32 uvw takes 128 registers either way and ran slower when
+// told so (39 / 41), and with fewer lanes the plan was never bound by the LDS.
+template <typename UT, int DC, int L>
+constexpr int most_waves()
+{
+    return L != 8 ? 8 : (DC == 8 ? 7 : (DC == 16 ? (sizeof(UT) == 2 ? 5 : 8) : 4));
+}
+
 // Pixel of ray slot `slot` in a wave's tile.  One lane per ray: Z order, so
 // that the four lanes of a quad are a block of 2 x 2 pixels, whose texels fall
 // in fewer 64-byte segments than those of four pixels in a row (a gather costs
@@ -1540,7 +1556,9 @@ __device__ __forceinline__ int32_t centre_first(int32_t k, int32_t n)
 }
 
 template <typename ST, typename UT, int DC, bool STATS, int L, bool SKIP, bool LIN, bool NDC>
-__global__ __launch_bounds__(kBlockThreads, (occupancy<UT, DC, LIN, NDC, L>())) void render_kernel(const RenderParams P)
+__global__ __launch_bounds__(kBlockThreads)
+__attribute__((amdgpu_waves_per_eu(occupancy<UT, DC, LIN, NDC, L>(), most_waves<UT, DC, L>())))
+void render_kernel(const RenderParams P)
 {
     // beta of every lane's ray, component-major so that a wave-wide read of
     // one component touches consecutive LDS words; each lane reads only what
