@@ -1009,8 +1009,8 @@ __device__ __forceinline__ void march_geometry(const RenderParams& P, const floa
 // the runs its lanes found).
 // COOP: the workgroup computed the ray's geometry and beta once per ray
 // (`pre`; beta at beta[k * BS]) instead of in each of its L lanes.
-template <typename ST, typename UT, int DC, bool STATS, int L, bool SKIP, bool LIN, bool NDC, bool COOP = false,
-          int BS = kBlockThreads>
+template <typename ST, typename UT, int DC, bool STATS, int L, bool SKIP, bool LIN, bool NDC, bool AHEAD,
+          bool COOP = false, int BS = kBlockThreads>
 __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, int32_t u,
                                            int32_t v, int32_t lane, float* const beta, float* const lin,
                                            const ColourQueue& cq, int32_t slot, const RayLds<NDC>* pre = nullptr)
@@ -1085,15 +1085,9 @@ __device__ __forceinline__ void render_ray(const RenderParams& P, int32_t view, 
     }
     uint32_t q_head = 0, q_count = 0;   // the wave's queue, wave-uniform
 
-    // With one or two lanes per ray and for Eq. 5 the next sample's gathers
-    // (Eq. 5: its cell's byte) are issued as soon as it is known to be needed,
-    // before the sample ahead of it is composited (weight, queue, drain), so
-    // that work hides their latency: one lane, 800x800, 256 samples of a 512
-    // cache 159 -> 148 us, 192 samples of a 256 cache 98 -> 96; Eq. 5 at 512
-    // 170 -> 165; two lanes 124 -> 122.  Four and eight lanes, bound by
-    // vector-ALU issue, lose more to the values kept live (504x378 in NDC 88
-    // -> 98 us), so there a sample is gathered when its turn comes.
-    constexpr bool kAhead = L <= 2 || LIN;
+    // the next sample's gathers (Eq. 5: its cell's byte) are issued as soon as
+    // it is known to be needed, or when its turn comes (gathers_ahead)
+    constexpr bool kAhead = AHEAD;
     using Rec = SigmaRecord<ST>;
     float t = 0.0f;
     uint32_t ix = 0, iy = 0, iz = 0;
@@ -1426,6 +1420,31 @@ constexpr int beta_smem_floats()
     return LIN ? 4 : (DC > 0 ? DC : 32) * (L == 1 ? kBlockThreads : rays_stride(L));
 }
 
+// Whether the march gathers its next sample as soon as it is known to be
+// needed, before the sample ahead of it is weighed and queued, so that this
+// work hides the gathers' latency.  With one or two lanes per ray and for Eq. 5:
+// one lane, 800x800, 256 samples of a 512 cache 159 -> 148 us, 192 samples of a
+// 256 cache 98 -> 96; Eq. 5 at 512 170 -> 165; two lanes 124 -> 122.  Four and
+// eight lanes, bound by vector-ALU issue, lose more to the values kept live
+// (504x378 in NDC 88 -> 98 us).  The two-word records of binary32 sigma beside
+// the binary16 uvw kernels' register budget (72 at D = 8) spill and lose in two
+// one-lane marches.  In NDC at D = 8: 1600x900x192 of a 512 cache 331 us without,
+// 346 with, the mean of eight views 2.5% slower (uvw alike or D = 16 are not:
+// 259 -> 253, 507 -> 490).  And in the one-lane part of a hybrid launch, whose
+// registers the four-lane part pays for too: 800x800 at D = 8, centred blocks of
+// 0.15 and 0.5, 133 -> 141 and 122 -> 126 us; at D = 16 blocks of 1 lose 13%,
+// 0.15 gain 5%; the other types gain 1-9% in every hybrid.
+template <typename ST, typename UT>
+constexpr bool mixed_types()
+{
+    return sizeof(ST) == 4 && sizeof(UT) == 2;
+}
+template <typename ST, typename UT, int DC, int L, bool LIN, bool NDC>
+constexpr bool gathers_ahead()
+{
+    return LIN || L == 2 || (L == 1 && !(mixed_types<ST, UT>() && NDC && DC == 8));
+}
+
 // Waves per SIMD: the register target, capped by how many 4-wave workgroups
 // the 160 KiB of LDS of a compute unit holds.
 template <typename UT, int DC, bool LIN, bool NDC = false, int L = 1>
@@ -1482,7 +1501,7 @@ __device__ __forceinline__ int32_t slot_y(int32_t slot)
 // One workgroup's rays at tile (tx, ty) of view `view`, with the LDS arrays
 // of the launch shape: beta, the Eq. 5 rows, the colour queue and sums, and
 // (four or eight lanes) the rays' march geometry.
-template <typename ST, typename UT, int DC, bool STATS, int L, bool SKIP, bool LIN, bool NDC>
+template <typename ST, typename UT, int DC, bool STATS, int L, bool SKIP, bool LIN, bool NDC, bool AHEAD>
 __device__ __forceinline__ void workgroup_rays(const RenderParams& P, int32_t view, int32_t tx, int32_t ty,
                                                float* beta_smem, float* lin_smem, uint4* queue_smem,
                                                double* qacc_smem, RayLds<NDC>* geom)
@@ -1532,8 +1551,9 @@ __device__ __forceinline__ void workgroup_rays(const RenderParams& P, int32_t vi
         cq.acc = qacc_smem + wave * RPW * 3;
         cq.beta = beta_smem + wave * RPW;
         if (view < P.n_views && u < P.width && v < P.height)
-            render_ray<ST, UT, DC, STATS, L, SKIP, LIN, NDC, true, RS>(P, view, u, v, lane, beta_smem + r,
-                                                                      LIN ? lin_row(r) : nullptr, cq, slot, &geom[r]);
+            render_ray<ST, UT, DC, STATS, L, SKIP, LIN, NDC, AHEAD, true, RS>(P, view, u, v, lane, beta_smem + r,
+                                                                             LIN ? lin_row(r) : nullptr, cq, slot,
+                                                                             &geom[r]);
     } else {
         // all lanes of a ray agree on this, so a lane group is never split
         static_assert(!LIN, "the Eq. 5 decoder runs with four lanes per ray");
@@ -1542,8 +1562,8 @@ __device__ __forceinline__ void workgroup_rays(const RenderParams& P, int32_t vi
             cq.entries = queue_smem + wave * kQueue;
             cq.acc = qacc_smem + wave * 64 * 3;
             cq.beta = beta_smem + wave * 64;
-            render_ray<ST, UT, DC, STATS, L, SKIP, LIN, NDC>(P, view, u, v, lane, beta_smem + threadIdx.x, nullptr,
-                                                        cq, slot);
+            render_ray<ST, UT, DC, STATS, L, SKIP, LIN, NDC, AHEAD>(P, view, u, v, lane, beta_smem + threadIdx.x,
+                                                               nullptr, cq, slot);
         }
     }
 }
@@ -1600,8 +1620,8 @@ void render_kernel(const RenderParams P)
         ty = tr / P.tiles_x;
         tx = tr - ty * P.tiles_x;
     }
-    workgroup_rays<ST, UT, DC, STATS, L, SKIP, LIN, NDC>(P, view, tx, ty, beta_smem, lin_smem, queue_smem, qacc_smem,
-                                                         geom_smem);
+    workgroup_rays<ST, UT, DC, STATS, L, SKIP, LIN, NDC, gathers_ahead<ST, UT, DC, L, LIN, NDC>()>(
+        P, view, tx, ty, beta_smem, lin_smem, queue_smem, qacc_smem, geom_smem);
 }
 
 // LDS bytes of one workgroup of a hybrid launch with L lanes per ray: the
@@ -1665,8 +1685,8 @@ __global__ __launch_bounds__(kBlockThreads, (hybrid_occupancy<UT, DC>())) void r
         }
         const int32_t by = P.hy_y0 + centre_first(blk / P.hy_w, P.hy_h);
         const int32_t bx = P.hy_x0 + centre_first(blk % P.hy_w, P.hy_w);
-        workgroup_rays<ST, UT, DC, STATS, 4, true, false, false>(P, 0, 2 * bx + (sub & 1), 2 * by + (sub >> 1), beta,
-                                                                 nullptr, queue, acc, geom);
+        workgroup_rays<ST, UT, DC, STATS, 4, true, false, false, false>(P, 0, 2 * bx + (sub & 1), 2 * by + (sub >> 1),
+                                                                        beta, nullptr, queue, acc, geom);
     } else {
         // the blocks outside the rectangle, row by row: the rows above it,
         // the rows beside it (left part, then right part), the rows below
@@ -1688,7 +1708,8 @@ __global__ __launch_bounds__(kBlockThreads, (hybrid_occupancy<UT, DC>())) void r
             by = P.hy_y0 + P.hy_h + r;
             bx = l - r * P.hy_bx;
         }
-        workgroup_rays<ST, UT, DC, STATS, 1, true, false, false>(P, 0, bx, by, beta, nullptr, queue, acc, nullptr);
+        workgroup_rays<ST, UT, DC, STATS, 1, true, false, false, !mixed_types<ST, UT>()>(P, 0, bx, by, beta, nullptr,
+                                                                                         queue, acc, nullptr);
     }
 }
 

@@ -60,3 +60,26 @@ def test_eight_lane_drains_gather_at_once(render_object, sigma, uvw, D, ndc):
     counts = _gathers_before_wait(_disassemble(render_object, _kernel(sigma, uvw, D, 8, ndc=ndc)))
     rounds = [n for n in counts if n]     # the other reads are of the ray setup
     assert len(rounds) >= 5 and min(rounds) >= 6, counts
+
+
+def _resources(path):
+    """{kernel name: (VGPRs, bytes of scratch per lane)} from the code object's
+    metadata."""
+    notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", path], check=True, capture_output=True,
+                           text=True).stdout
+    out = {}
+    for entry in notes.split("- .agpr_count:")[1:]:
+        value = lambda key: re.search(rf"\.{key}:\s+(\S+)", entry).group(1)
+        out[value("name")] = (int(value("vgpr_count")), int(value("private_segment_fixed_size")))
+    return out
+
+
+def test_marches_that_lost_to_spills_spill_nothing(render_object):
+    """binary32 sigma beside binary16 uvw at D = 8: the one-lane march in NDC and
+    the hybrid launch keep their 72 registers (7 waves per SIMD) without
+    scratch."""
+    found = _resources(render_object)
+    hybrid = "_ZN3sqn12_GLOBAL__N_120render_kernel_hybridIfDF16_Li8ELb0EEEvNS_12RenderParamsE"
+    for name in (_kernel("f32", "f16", 8, 1, ndc=True), hybrid):
+        vgprs, scratch = found[name]
+        assert vgprs <= 72 and scratch == 0, (name, vgprs, scratch)
