@@ -470,7 +470,7 @@ def main():
         lanes = caches.tune_lanes_per_ray(poses, scene.intrinsics, scene.near, scene.far, N, rgb, depth,
                                           stream=stream)
         centre = caches.centre_block
-        shape_label = f"tuned: hybrid {centre:g}" if lanes == -1 else f"tuned: {lanes}"
+        shape_label = f"tuned: hybrid {centre:g}" if lanes == -1 else f"tuned: {lanes or 'auto'}"
     else:
         if lanes == 0 and centre == 0.0 and not args.dense:
             lanes, centre = LAUNCH_SHAPES.get(cfg.name, (0, 0.0))

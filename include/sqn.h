@@ -248,7 +248,8 @@ sqn_status sqn_set_lanes_per_ray(sqn_caches* caches, int32_t lanes);
 sqn_status sqn_set_centre_block(sqn_caches* caches, float fraction);
 
 /* Measure the launch shapes on one batch and keep the fastest: renders the
- * batch (arguments as sqn_render) with 4, 1 and 8 lanes per ray and, for a
+ * batch (arguments as sqn_render) with 4, 1 and 8 lanes per ray, in the
+ * automatic choice where that is two lanes, and, for a
  * single view where sqn_set_centre_block applies, with hybrid launches of
  * centred fractions 0.15, 0.5 and 1 (four lanes only for a handle made by
  * sqn_create_linear_caches): each twice untimed, then in four rounds that
@@ -257,13 +258,13 @@ sqn_status sqn_set_centre_block(sqn_caches* caches, float fraction);
  * they settle over all candidates), then keeps the fastest (least total
  * time) as sqn_set_lanes_per_ray
  * and sqn_set_centre_block would, and writes the choice to lanes_out (the
- * lanes per ray, or -1 for a hybrid launch) and centre_out (the hybrid
+ * lanes per ray, 0 for the automatic choice, or -1 for a hybrid launch) and
+ * centre_out (the hybrid
  * fraction, 0 otherwise) where they are not NULL (for an empty batch the
  * settings stay and nothing is written).  No candidate changes a sample, index or
  * termination decision, only the time; which is fastest depends on the
  * image size, the number of views and the scene (the chains of samples),
- * which the default per-call choice (which has two lanes besides) sees only
- * through the number of rays.
+ * which the default per-call choice sees only through the number of rays.
  * A single view deals its tiles in blocks of 2 x 2 from the centre of the
  * image outwards.  rgb_out and depth_out receive a render of
  * the batch.  Blocks until the timed renders finish; creates two HIP events

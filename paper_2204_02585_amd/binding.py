@@ -297,8 +297,8 @@ class Caches:
                            n_samples: int, rgb_out: Optional[torch.Tensor] = None,
                            depth_out: Optional[torch.Tensor] = None, stream=None) -> int:
         """sqn_tune_lanes_per_ray: time the launch shapes on this batch, keep
-        the fastest for later renders and return it: lanes per ray, or -1 for
-        a hybrid launch, whose centre fraction is then in self.centre_block.
+        the fastest for later renders and return it: lanes per ray, 0 for the
+        automatic choice (where that is two lanes), or -1 for a hybrid launch, whose centre fraction is then in self.centre_block.
         Blocks; rgb_out / depth_out (allocated if not given) receive a
         render."""
         poses = _poses_arg(poses)

@@ -1168,13 +1168,21 @@ sqn_status sqn_tune_lanes_per_ray(sqn_caches* caches, const float* poses, int32_
     const int32_t before = caches->lanes;
     const float centre_before = caches->centre;
     // the batch itself is checked by the first render; candidates: lanes
-    // per ray (centre 0), then hybrid launches of single views with centred
+    // per ray (centre 0), the automatic choice where that is the two lanes
+    // which cannot be set, then hybrid launches of single views with centred
     // blocks of 0.15, 0.5 and 1 of the image per axis (1: four lanes per ray
     // everywhere, blocks dealt from the centre outwards)
-    static const int32_t kCandidates[6] = {4, 1, 8, 0, 0, 0};
-    static const float kCentre[6] = {0.0f, 0.0f, 0.0f, 0.15f, 0.5f, 1.0f};
-    const bool hybrid_ok = n_poses == 1 && !caches->linear && caches->skip && !(caches->ndc_near > 0.0f);
-    const int n_cand = caches->linear ? 1 : (hybrid_ok ? 6 : 3);
+    struct {
+        int32_t lanes;
+        float centre;
+    } shapes[7] = {{4, 0.0f}, {1, 0.0f}, {8, 0.0f}};
+    int n_cand = caches->linear ? 1 : 3;
+    if (!caches->linear && intrinsics && n_poses > 0
+        && choose_lanes(static_cast<int64_t>(n_poses) * intrinsics->width * intrinsics->height, caches->skip != 0) == 2)
+        shapes[n_cand++] = {0, 0.0f};
+    if (n_poses == 1 && !caches->linear && caches->skip && !(caches->ndc_near > 0.0f))
+        for (const float centre : {0.15f, 0.5f, 1.0f})
+            shapes[n_cand++] = {0, centre};
     // every candidate twice untimed (code and caches warm), then kRounds
     // rounds that each time every candidate over kReps renders (after one
     // untimed render in its shape): the GPU's clocks settle over the first
@@ -1191,10 +1199,10 @@ sqn_status sqn_tune_lanes_per_ray(sqn_caches* caches, const float* poses, int32_
             return fail(SQN_ERR_DEVICE, "hipEventCreate failed");
         }
     sqn_status s = SQN_OK;
-    float total_ms[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    float total_ms[7] = {};
     auto render = [&](int c, int times) {
-        caches->lanes = kCandidates[c];
-        caches->centre = kCentre[c];
+        caches->lanes = shapes[c].lanes;
+        caches->centre = shapes[c].centre;
         for (int r = 0; r < times && s == SQN_OK; ++r)
             s = render_common(caches, poses, n_poses, intrinsics, near_plane, far_plane, n_samples, rgb_out,
                               depth_out, nullptr, stream);
@@ -1236,12 +1244,12 @@ sqn_status sqn_tune_lanes_per_ray(sqn_caches* caches, const float* poses, int32_
         caches->centre = centre_before;
         return s;
     }
-    caches->lanes = kCandidates[best];
-    caches->centre = kCentre[best];
+    caches->lanes = shapes[best].lanes;
+    caches->centre = shapes[best].centre;
     if (lanes_out)
-        *lanes_out = kCentre[best] > 0.0f ? -1 : kCandidates[best];
+        *lanes_out = shapes[best].centre > 0.0f ? -1 : shapes[best].lanes;
     if (centre_out)
-        *centre_out = kCentre[best];
+        *centre_out = shapes[best].centre;
     return SQN_OK;
 }
 

@@ -1,0 +1,44 @@
+"""Choices of the library's host code, on the CPU (tests/fake_hip.py): which
+kernel a render launches, what tuning keeps, whether every accepted size is a
+legal launch, and what a create does when memory is short."""
+import pytest
+
+from tests import fake_hip
+
+# 800 x 800 x 256 of a 512 cache, ms per launch in each shape
+COSTS = """
+for part, ms in ((b"render_kernel_hybrid", 0.145), (b"ELi1ELb1ELb0", 0.149), (b"ELi2ELb1ELb0", 0.122),
+                 (b"ELi4ELb1ELb0", 0.135), (b"ELi8ELb1ELb0", 0.174)):
+    fake.fake_cost(part, ms)
+"""
+
+
+def test_tuning_keeps_the_automatic_two_lanes_where_they_are_fastest():
+    """The shape that a render takes without tuning is among the candidates, so
+    tuning never leaves a handle in a slower one."""
+    got = fake_hip.run("""
+d = desc(512, 8, sigma="f32")
+a = arrays(d)
+h = ctypes.c_void_p()
+assert lib.sqn_create_caches(ctypes.byref(d), a[0], a[1], a[2], None, ctypes.byref(h)) == 0
+out = []
+for w, n in ((800, 1), (400, 3), (200, 1), (1600, 1)):
+    it = intrinsics(w, w)
+    poses, rgb, depth = alloc(48 * n), alloc(12 * w * w * n), alloc(4 * w * w * n)
+    fake.fake_reset()
+""" + COSTS.replace("\n", "\n    ") + """
+    lanes, centre = ctypes.c_int32(-7), ctypes.c_float(-7)
+    assert lib.sqn_tune_lanes_per_ray(h, poses, n, ctypes.byref(it), 2.0, 6.0, 256, rgb, depth, None,
+                                      ctypes.byref(lanes), ctypes.byref(centre)) == 0
+    launches()
+    assert lib.sqn_render(h, poses, n, ctypes.byref(it), 2.0, 6.0, 256, rgb, depth, None) == 0
+    out.append([lanes.value, centre.value, launches()])
+print(json.dumps(out))
+""")
+    # one view and three views between 2^18 and 2^20 rays: two lanes, by the
+    # automatic choice; outside, where it is eight or one lanes, what is
+    # fastest of the lane counts that can be set
+    for lanes, centre, log in got[:2]:
+        assert (lanes, centre) == (0, 0.0) and len(log) == 1 and "ELi2ELb1ELb0" in log[0], got
+    for lanes, centre, log in got[2:]:
+        assert (lanes, centre) == (4, 0.0) and "ELi4ELb1ELb0" in log[0], got
