@@ -223,8 +223,8 @@ sqn_status sqn_render_stats(const sqn_caches* caches,
 /* Launch shape of later renders with this handle: how many lanes of a
  * wavefront share one ray (1, 4 or 8; the L lanes take the L consecutive
  * samples of a chunk), or 0 (the default) to choose per call from the number
- * of rays (8 below 2^18 rays, below 2^20 two, or 4 for the dense march, else
- * 1).  Sample, index and termination decisions are identical for every
+ * of rays (8 below 2^18 rays, below 2^20 two, or 4 for the dense march, D
+ * above 16 and some kinds of view, else 1).  Sample, index and termination decisions are identical for every
  * choice; colour and depth agree up to the rounding of their sums.  Not
  * thread-safe against concurrent renders with the handle.
  * Errors: SQN_ERR_INVALID_ARG; SQN_ERR_UNSUPPORTED for 1 or 8 on a handle

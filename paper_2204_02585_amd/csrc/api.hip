@@ -228,10 +228,27 @@ sqn_status validate_decoder(const sqn_linear_decoder* dec, int32_t D)
 // line 1314x865 94 / 109 / 144 / 205.  Below 2^18 rays the chip is not full
 // for one round of two-lane waves and eight lanes shorten the chains again
 // (504x378 forward-facing 213 / 127 / 101 / 89, 287x276 91 / 58 / 51 / 38).
-// The dense march, whose chains are alike, keeps four lanes in between.
-int choose_lanes(int64_t rays, bool skip)
+// The dense march, whose chains are alike, keeps four lanes in between, and so
+// does any D without a kernel of its own, which evaluates colour where the
+// sample is found while the wave's other rays wait (D = 24, 800x800, two / four
+// lanes: 1,390 / 978 us with binary32 uvw, 1,460 / 1,347 with binary16, 2,890 /
+// 2,040 in NDC).  Near the lower line two lanes lose on the kinds of view whose
+// chains are short or alike across a wave: D = 8 in batches of views, or with
+// binary16 uvw in NDC, and D = 16 with binary32 uvw in NDC.  Four lanes took, in
+// the mean over 51 random views of these kinds with 2^18 to 3 * 2^17 rays, 0.92
+// to 0.95 of the time of two, and over 129 with more 1.03 to 1.06; the other
+// kinds 1.00 to 1.14 in the lower range and 1.09 to 1.27 above.
+int choose_lanes(const sqn_caches* h, int32_t n_poses, int64_t rays)
 {
-    return rays < (int64_t{1} << 18) ? 8 : (rays < (int64_t{1} << 20) ? (skip ? 2 : 4) : 1);
+    if (rays < (int64_t{1} << 18))
+        return 8;
+    if (rays >= (int64_t{1} << 20))
+        return 1;
+    if (!h->skip || (h->D != 8 && h->D != 16))
+        return 4;
+    const bool ndc = h->ndc_near > 0.0f, uvw16 = h->desc.uvw_dtype == SQN_F16;
+    const bool late = h->D == 8 ? (ndc ? uvw16 : n_poses > 1) : (ndc && !uvw16);
+    return late && rays < (int64_t{3} << 17) ? 4 : 2;
 }
 
 sqn_status render_common(const sqn_caches* h, const float* poses, int32_t n_poses,
@@ -297,7 +314,7 @@ sqn_status render_common(const sqn_caches* h, const float* poses, int32_t n_pose
     p.skip = h->skip;
     // the folded Eq. 5 weights are shared by the lanes of a ray in LDS, which
     // holds them for 64 rays per workgroup, i.e. four lanes per ray
-    p.lanes = h->linear ? 4 : (h->lanes != 0 ? h->lanes : choose_lanes(rays, h->skip != 0));
+    p.lanes = h->linear ? 4 : (h->lanes != 0 ? h->lanes : choose_lanes(h, n_poses, rays));
     p.linear = h->linear;
     p.b_sigma = h->b_sigma;
     p.lin_w = h->lin_w;
@@ -1178,7 +1195,7 @@ sqn_status sqn_tune_lanes_per_ray(sqn_caches* caches, const float* poses, int32_
     } shapes[7] = {{4, 0.0f}, {1, 0.0f}, {8, 0.0f}};
     int n_cand = caches->linear ? 1 : 3;
     if (!caches->linear && intrinsics && n_poses > 0
-        && choose_lanes(static_cast<int64_t>(n_poses) * intrinsics->width * intrinsics->height, caches->skip != 0) == 2)
+        && choose_lanes(caches, n_poses, static_cast<int64_t>(n_poses) * intrinsics->width * intrinsics->height) == 2)
         shapes[n_cand++] = {0, 0.0f};
     if (n_poses == 1 && !caches->linear && caches->skip && !(caches->ndc_near > 0.0f))
         for (const float centre : {0.15f, 0.5f, 1.0f})

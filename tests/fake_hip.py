@@ -62,15 +62,16 @@ def intrinsics(w, h):
 """
 
 
-def run(code, timeout=100):
-    """The JSON that `code` prints last, run behind PRELUDE."""
+def run(code, data=None, timeout=100):
+    """The JSON that `code` prints last, run behind PRELUDE with `data` (plain
+    values) as DATA."""
     build = os.path.join(HERE, "..", "paper_2204_02585_amd", "_build")
     os.makedirs(build, exist_ok=True)
     lib = os.path.abspath(os.path.join(build, f"fake_hip_{os.getpid()}.so"))
     try:
         subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", lib, os.path.join(HERE, "fake_hip.c")],
                        check=True)
-        script = f"ROOT, FAKE = {ROOT!r}, {lib!r}\n" + PRELUDE + code
+        script = f"ROOT, FAKE, DATA = {ROOT!r}, {lib!r}, {data!r}\n" + PRELUDE + code
         p = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=timeout)
         assert p.returncode == 0, p.stderr[-3000:]
         return json.loads(p.stdout.splitlines()[-1])

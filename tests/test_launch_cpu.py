@@ -42,3 +42,48 @@ print(json.dumps(out))
         assert (lanes, centre) == (0, 0.0) and len(log) == 1 and "ELi2ELb1ELb0" in log[0], got
     for lanes, centre, log in got[2:]:
         assert (lanes, centre) == (4, 0.0) and "ELi4ELb1ELb0" in log[0], got
+
+
+# D, uvw, NDC, views, width, height, leaps -> lanes
+LANES = [
+    (8, "f16", 0, 1, 512, 511, 1, 8), (8, "f16", 0, 1, 512, 512, 1, 2), (8, "f32", 0, 1, 1024, 1023, 1, 2),
+    (8, "f16", 0, 1, 1024, 1024, 1, 1), (16, "f32", 0, 1, 512, 512, 1, 2), (12, "f16", 0, 1, 512, 512, 1, 2),
+    # no leaps, and D without a kernel of its own
+    (8, "f16", 0, 1, 800, 800, 0, 4), (24, "f16", 0, 1, 800, 800, 1, 4), (17, "f32", 1, 1, 512, 512, 1, 4),
+    (32, "f32", 0, 1, 512, 511, 1, 8), (24, "f16", 0, 1, 1024, 1024, 1, 1),
+    # two lanes from 3 * 2^17 rays
+    (8, "f16", 0, 2, 512, 383, 1, 4), (8, "f16", 0, 2, 512, 384, 1, 2), (8, "f32", 0, 3, 300, 300, 1, 4),
+    (8, "f16", 1, 1, 768, 511, 1, 4), (8, "f16", 1, 1, 768, 512, 1, 2), (8, "f16", 1, 2, 512, 383, 1, 4),
+    (16, "f32", 1, 1, 768, 511, 1, 4), (16, "f32", 1, 1, 768, 512, 1, 2),
+    # the same kinds in the other type or D, from 2^18
+    (8, "f32", 1, 1, 512, 512, 1, 2), (8, "f32", 1, 2, 512, 383, 1, 2), (16, "f16", 1, 1, 512, 512, 1, 2),
+    (16, "f16", 0, 2, 512, 383, 1, 2), (16, "f32", 0, 2, 512, 383, 1, 2),
+]
+
+
+def test_automatic_lanes():
+    """Lanes per ray by rays, views, D, uvw type and ray space: the name of the
+    launched kernel carries them."""
+    got = fake_hip.run(r"""
+import re
+out = []
+for D, uvw, ndc, views, w, height, skip in DATA:
+    d = desc(64, D, uvw=uvw)
+    a = arrays(d)
+    h = ctypes.c_void_p()
+    assert lib.sqn_create_caches(ctypes.byref(d), a[0], a[1], a[2], None, ctypes.byref(h)) == 0
+    assert lib.sqn_set_ndc(h, 1.0 if ndc else 0.0) == 0 and lib.sqn_set_empty_space_skipping(h, skip) == 0
+    it = intrinsics(w, height)
+    poses, rgb, depth = alloc(48 * views), alloc(12 * w * height * views), alloc(4 * w * height * views)
+    fake.fake_reset()
+    assert lib.sqn_render(h, poses, views, ctypes.byref(it), 0.5, 1.0, 64, rgb, depth, None) == 0
+    log = launches()
+    assert len(log) == 1, log
+    out.append(int(re.search(r"render_kernelI\w+?Li\d+ELb0ELi(\d+)E", log[0]).group(1)))
+    lib.sqn_destroy(h)
+    for p in (poses, rgb, depth):
+        fake.hipFree(p)
+    free(a)
+print(json.dumps(out))
+""", data=[c[:7] for c in LANES])
+    assert [(c, lanes) for c, lanes in zip(LANES, got) if lanes != c[7]] == []
