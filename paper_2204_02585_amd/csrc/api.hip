@@ -395,9 +395,18 @@ struct CacheLayout {
 // add exactly nothing to a dot product).  617 x 463 x 200 of a 384 cache, D =
 // 12: 0.42 ms on the kernel for any D (one load per component), 0.14 ms filled
 // up to 16; 72-byte records become 96, which counts only where HBM bounds a
-// view.  Any other D, and planes that would pass 2^32 bytes, stay as they are.
-int32_t stored_components(const sqn_cache_desc* desc)
+// view.  Planes that would pass 2^32 bytes stay as they are, and so do Eq. 4's
+// narrowest records, whose texels share so many cache lines that four to eight
+// times the bytes cost more than the loads: 800 x 640 x 110 of a 1400 cache,
+// binary32, D = 1 94 us as they are and 178 filled, D = 2 132 and 165;
+// binary16, D = 1 109 and 148 (a small cache gains as much as a large one
+// loses).  With binary16 D = 2 gains (400 cache 69 -> 51 us, 1400 cache 255 ->
+// 264), D = 3 in both types (91 -> 56, 173 -> 141), and Eq. 5, whose any-D kernel
+// is bound by LDS, for every D (D = 1: 513 -> 160).
+int32_t stored_components(const sqn_cache_desc* desc, bool linear)
 {
+    if (!linear && (desc->D == 1 || (desc->D == 2 && desc->uvw_dtype != SQN_F16)))
+        return desc->D;
     const int32_t D = desc->D <= 8 ? 8 : (desc->D <= 16 ? 16 : desc->D);
     const uint64_t plane = static_cast<uint64_t>(desc->n_p) * desc->n_p * 3u * D * dtype_size(desc->uvw_dtype);
     const uint64_t beta = static_cast<uint64_t>(desc->n_theta) * desc->n_phi * D * dtype_size(desc->beta_dtype);
@@ -629,7 +638,7 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     const int32_t ds = linear ? dec->d_sigma : 1;
     const size_t texels = static_cast<size_t>(desc->n_p) * desc->n_p;
     const size_t sigma_bytes = texels * ds * dtype_size(desc->sigma_dtype);
-    const CacheLayout lay = cache_layout(desc, linear, stored_components(desc));
+    const CacheLayout lay = cache_layout(desc, linear, stored_components(desc, linear));
     const int32_t D = lay.D, Du = desc->D;   // stored, and the caller's
     const size_t uvw_bytes = lay.uvw_bytes / D * Du, beta_bytes = lay.beta_bytes / D * Du, lin_bytes = lay.lin_bytes;
     const size_t lin_rows = 9 * static_cast<size_t>(D) + 3;
@@ -895,7 +904,7 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     if (device != caches->device)
         return fail(SQN_ERR_INVALID_ARG, "caches live on device %d, current device is %d", caches->device, device);
     // records filled up where the block has room for them
-    CacheLayout lay = cache_layout(desc, false, stored_components(desc));
+    CacheLayout lay = cache_layout(desc, false, stored_components(desc, false));
     if (lay.total > caches->bytes)
         lay = cache_layout(desc, false, desc->D);
     if (lay.total > caches->bytes)

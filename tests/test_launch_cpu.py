@@ -87,3 +87,43 @@ for D, uvw, ndc, views, w, height, skip in DATA:
 print(json.dumps(out))
 """, data=[c[:7] for c in LANES])
     assert [(c, lanes) for c, lanes in zip(LANES, got) if lanes != c[7]] == []
+
+
+def test_stored_components():
+    """Which records are filled up: the handle's bytes and the kernel's D."""
+    cases = [("f16", 1, 0, 0), ("f32", 1, 0, 0), ("f16", 2, 0, 8), ("f32", 2, 0, 0), ("f16", 3, 0, 8), ("f32", 3, 0, 8),
+             ("f16", 8, 0, 8), ("f16", 9, 0, 16), ("f32", 16, 0, 16), ("f16", 17, 0, 0), ("f16", 1, 1, 8),
+             ("f32", 2, 1, 8), ("f32", 12, 1, 16), ("f16", 31, 1, 0)]
+    got = fake_hip.run(r"""
+import re
+import numpy as np
+out = []
+for uvw, D, linear, _ in DATA:
+    d = desc(64, D, uvw=uvw)
+    a = arrays(d)
+    h = ctypes.c_void_p()
+    if linear:
+        w = [np.zeros(n, np.float32) for n in (3, 9 * D * D, 3 * D)]
+        dec = B.LinearDecoder(1, 0.5, *[x.ctypes.data for x in w])
+        s = lib.sqn_create_linear_caches(ctypes.byref(d), ctypes.byref(dec), a[0], a[1], a[2], None, ctypes.byref(h))
+    else:
+        s = lib.sqn_create_caches(ctypes.byref(d), a[0], a[1], a[2], None, ctypes.byref(h))
+    assert s == 0, B.last_error()
+    it = intrinsics(64, 64)
+    poses, rgb, depth = alloc(48), alloc(12 * 4096), alloc(4 * 4096)
+    fake.fake_reset()
+    assert lib.sqn_render(h, poses, 1, ctypes.byref(it), 0.5, 1.0, 64, rgb, depth, None) == 0
+    out.append([int(re.search(r"render_kernelI\w+?Li(\d+)ELb0E", launches()[0]).group(1)), lib.sqn_cache_device_bytes(h)])
+    lib.sqn_destroy(h)
+    for p in (poses, rgb, depth):
+        fake.hipFree(p)
+    free(a)
+print(json.dumps(out))
+""", data=cases)
+    for (uvw, D, linear, kernel), (launched, nbytes) in zip(cases, got):
+        assert launched == kernel, (uvw, D, linear, launched)
+        if not linear:
+            # 64 x 64 texels in three planes (4-byte sigma records), 256
+            # directions in binary16; every part a multiple of 256 bytes
+            stored = kernel or D
+            assert nbytes == 3 * 4096 * (4 + 3 * stored * (2 if uvw == "f16" else 4)) + 256 * stored * 2, (uvw, D)
