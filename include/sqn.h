@@ -110,6 +110,12 @@ typedef struct {
  *                    for them, so the caller may free its arrays on return.
  * Values must be finite.  On success *out owns the copy (free it with
  * sqn_destroy); on failure *out is NULL and nothing is leaked.
+ * The copy takes more memory than the arrays (sqn_cache_device_bytes): a
+ * distance beside each sigma, and colour records, in uvw and beta, filled up to
+ * 8 or 16 components where D is smaller (not for D = 1, nor D = 2 in binary32)
+ * and a filled plane stays below 2^32 bytes.  Where there is no memory for the
+ * filled records they are kept at D components, which renders up to nine
+ * times slower (the kernel for any D).
  * Errors: SQN_ERR_INVALID_ARG (NULL pointer, range, a pointer that is not
  * HIP device memory or whose allocation is smaller than the array),
  * SQN_ERR_UNSUPPORTED (a uvw plane or the direction cache of 2^32 bytes or
@@ -164,7 +170,9 @@ sqn_status sqn_create_linear_caches(const sqn_cache_desc* desc,
  * allocating nothing.  The handle (made by sqn_create_caches, Eq. 4) then
  * holds the caches desc describes; its lanes, leap and NDC settings stay.
  *   caches:      the handle; its device block must hold the new layout
- *                (sqn_cache_device_bytes of a handle created from desc);
+ *                (sqn_cache_device_bytes of a handle created from desc; a
+ *                block that has room for the records at D components, but
+ *                not filled up, takes them so);
  *   desc, sigma_planes, uvw_planes, beta: as for sqn_create_caches, with
  *                n_p <= 2048;
  *   stream:      hipStream_t the work is ordered on.

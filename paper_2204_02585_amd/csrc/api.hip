@@ -618,6 +618,32 @@ hipError_t copy_uvw_beta(const sqn_cache_desc* desc, const void* const uvw[3], c
     return hipGetLastError();
 }
 
+// The block of a handle laid out as `lay`, and the preparation's scratch: in
+// the block, or an allocation of its own (*work, freed by the caller after the
+// preparation) where the block has no room for it.  On failure neither is kept.
+hipError_t allocate(const sqn_cache_desc* desc, bool linear, const CacheLayout& lay, void** block, void** work,
+                    sqn::PrepareWork* pw)
+{
+    *work = nullptr;
+    hipError_t e = hipMalloc(block, lay.total);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
+    const size_t need = prepare_work(desc, linear, static_cast<char*>(*block) + lay.off_uvw[0], pw);
+    if (need <= late_bytes(lay))
+        return hipSuccess;
+    e = hipMalloc(work, need);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(*block);
+        *block = nullptr;
+        return e;
+    }
+    prepare_work(desc, linear, static_cast<char*>(*work), pw);
+    return hipSuccess;
+}
+
 // Shared body of the two create calls; dec == NULL selects Eq. 4.
 sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec,
                        const void* const sigma_planes[3], const void* const uvw_planes[3],
@@ -638,10 +664,8 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     const int32_t ds = linear ? dec->d_sigma : 1;
     const size_t texels = static_cast<size_t>(desc->n_p) * desc->n_p;
     const size_t sigma_bytes = texels * ds * dtype_size(desc->sigma_dtype);
-    const CacheLayout lay = cache_layout(desc, linear, stored_components(desc, linear));
-    const int32_t D = lay.D, Du = desc->D;   // stored, and the caller's
-    const size_t uvw_bytes = lay.uvw_bytes / D * Du, beta_bytes = lay.beta_bytes / D * Du, lin_bytes = lay.lin_bytes;
-    const size_t lin_rows = 9 * static_cast<size_t>(D) + 3;
+    const size_t uvw_bytes = texels * 3 * desc->D * dtype_size(desc->uvw_dtype);
+    const size_t beta_bytes = static_cast<size_t>(desc->n_theta) * desc->n_phi * desc->D * dtype_size(desc->beta_dtype);
     const int32_t cell_shift = sqn::linear_cell_shift(desc->n_p);
     const int32_t cell_m = sqn::linear_cells(desc->n_p);
     static const char* names_s[3] = {"sigma_planes[0] (xy)", "sigma_planes[1] (yz)", "sigma_planes[2] (zx)"};
@@ -655,9 +679,36 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     if ((s = check_device_range(beta, beta_bytes, "beta")) != SQN_OK)
         return s;
 
-    const size_t* off_sigma = lay.off_sigma;
-    const size_t* off_uvw = lay.off_uvw;
-    const size_t off_beta = lay.off_beta, off_lin = lay.off_lin, off_cells = lay.off_cells, total = lay.total;
+    sqn_caches* h = static_cast<sqn_caches*>(calloc(1, sizeof(sqn_caches)));
+    if (!h)
+        return fail(SQN_ERR_OUT_OF_MEMORY, "host allocation failed");
+    h->desc = *desc;
+    if (hipGetDevice(&h->device) != hipSuccess) {
+        free(h);
+        return fail(SQN_ERR_DEVICE, "hipGetDevice failed");
+    }
+    // records filled up where there is memory for them
+    CacheLayout lay = cache_layout(desc, linear, stored_components(desc, linear));
+    if (getenv("SQN_TEST_FAIL_ALLOC") != nullptr) {
+        free(h);
+        return fail(SQN_ERR_OUT_OF_MEMORY, "device allocation of %zu bytes refused (SQN_TEST_FAIL_ALLOC)", lay.total);
+    }
+    sqn::PrepareWork pw;
+    void* work = nullptr;
+    hipError_t e = allocate(desc, linear, lay, &h->block, &work, &pw);
+    if (e != hipSuccess && lay.D != desc->D) {
+        lay = cache_layout(desc, linear, desc->D);
+        e = allocate(desc, linear, lay, &h->block, &work, &pw);
+    }
+    if (e != hipSuccess) {
+        free(h);
+        return fail(SQN_ERR_OUT_OF_MEMORY, "hipMalloc(%zu) failed: %s", lay.total, hipGetErrorString(e));
+    }
+    h->bytes = lay.total;
+    char* base = static_cast<char*>(h->block);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const int32_t D = lay.D, Du = desc->D;   // stored, and the caller's
+    const size_t lin_rows = 9 * static_cast<size_t>(D) + 3;
 
     // host-side parameters of the linear decoder: the radiance weights
     // transposed so that row c*3D + e holds W_c[0..D)[e], followed
@@ -677,56 +728,19 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
                 lin_host[(9 * static_cast<size_t>(D) + c) * D + d] = dec->b_uvw[c * Du + d];
     }
 
-    sqn_caches* h = static_cast<sqn_caches*>(calloc(1, sizeof(sqn_caches)));
-    if (!h)
-        return fail(SQN_ERR_OUT_OF_MEMORY, "host allocation failed");
-    h->desc = *desc;
-    if (hipGetDevice(&h->device) != hipSuccess) {
-        free(h);
-        return fail(SQN_ERR_DEVICE, "hipGetDevice failed");
-    }
-    if (getenv("SQN_TEST_FAIL_ALLOC") != nullptr) {
-        free(h);
-        return fail(SQN_ERR_OUT_OF_MEMORY, "device allocation of %zu bytes refused (SQN_TEST_FAIL_ALLOC)", total);
-    }
-    hipError_t e = hipMalloc(&h->block, total);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        free(h);
-        return fail(SQN_ERR_OUT_OF_MEMORY, "hipMalloc(%zu) failed: %s", total, hipGetErrorString(e));
-    }
-    h->bytes = total;
-    char* base = static_cast<char*>(h->block);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    // scratch of the preparation, an allocation of its own (freed before
-    // returning) only where the block has no room for it
-    sqn::PrepareWork pw;
-    char* work = nullptr;
-    const size_t work_total = prepare_work(desc, linear, base + off_uvw[0], &pw);
-    if (work_total > late_bytes(lay)) {
-        e = hipMalloc(reinterpret_cast<void**>(&work), work_total);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipFree(h->block);
-            free(h);
-            return fail(SQN_ERR_OUT_OF_MEMORY, "hipMalloc of %zu scratch bytes failed", work_total);
-        }
-        prepare_work(desc, linear, work, &pw);
-    }
-
     void* packed[3];
     for (int j = 0; j < 3; ++j) {
-        packed[j] = base + off_sigma[j];
+        packed[j] = base + lay.off_sigma[j];
         h->sigma[j] = packed[j];
-        h->uvw[j] = base + off_uvw[j];
+        h->uvw[j] = base + lay.off_uvw[j];
     }
-    h->beta = base + off_beta;
+    h->beta = base + lay.off_beta;
     if (linear) {
-        e = hipMemcpyAsync(base + off_lin, lin_host.data(), lin_bytes, hipMemcpyHostToDevice, st);
+        e = hipMemcpyAsync(base + lay.off_lin, lin_host.data(), lay.lin_bytes, hipMemcpyHostToDevice, st);
         if (e == hipSuccess)
             e = sqn::prepare_linear_planes(sigma_planes, desc->sigma_dtype, desc->n_p, ds, dec->w_sigma, dec->b_sigma,
-                                           packed, cell_shift, cell_m, reinterpret_cast<uint8_t*>(base + off_cells),
-                                           pw, st);
+                                           packed, cell_shift, cell_m,
+                                           reinterpret_cast<uint8_t*>(base + lay.off_cells), pw, st);
     } else {
         e = sqn::prepare_sigma_planes(sigma_planes, desc->sigma_dtype, desc->n_p, packed, pw, st);
     }
@@ -753,8 +767,8 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
         h->linear = 1;
         h->d_sigma = ds;
         h->b_sigma = dec->b_sigma;
-        h->lin_w = reinterpret_cast<const float*>(base + off_lin);
-        h->cell_dist = reinterpret_cast<const uint8_t*>(base + off_cells);
+        h->lin_w = reinterpret_cast<const float*>(base + lay.off_lin);
+        h->cell_dist = reinterpret_cast<const uint8_t*>(base + lay.off_cells);
         h->cell_shift = cell_shift;
         h->cell_m = cell_m;
     }

@@ -127,3 +127,70 @@ print(json.dumps(out))
             # directions in binary16; every part a multiple of 256 bytes
             stored = kernel or D
             assert nbytes == 3 * 4096 * (4 + 3 * stored * (2 if uvw == "f16" else 4)) + 256 * stored * 2, (uvw, D)
+
+
+@pytest.mark.parametrize("linear", [0, 1])
+def test_create_without_memory_for_filled_records(linear):
+    """Too little memory for records of D = 4 filled up to 8, enough for them as
+    they are: the create succeeds with the narrow ones; with less it reports
+    it and keeps nothing."""
+    got = fake_hip.run(r"""
+import re
+import numpy as np
+D, n_p = 4, 64
+d = desc(n_p, D)
+a = arrays(d)
+rng = np.random.Generator(np.random.PCG64(1))
+w = [rng.uniform(-1, 1, n).astype(np.float32) for n in (3, 9 * D * D, 3 * D)]
+dec = B.LinearDecoder(1, 0.5, *[x.ctypes.data for x in w])
+def create():
+    h = ctypes.c_void_p()
+    if DATA:
+        s = lib.sqn_create_linear_caches(ctypes.byref(d), ctypes.byref(dec), a[0], a[1], a[2], None, ctypes.byref(h))
+    else:
+        s = lib.sqn_create_caches(ctypes.byref(d), a[0], a[1], a[2], None, ctypes.byref(h))
+    return s, h
+before = fake.fake_used()
+s, h = create()
+assert s == 0
+filled = lib.sqn_cache_device_bytes(h)
+lib.sqn_destroy(h)
+assert fake.fake_used() == before
+out = dict(filled=filled, tries=[])
+it = intrinsics(64, 64)
+poses, rgb, depth = alloc(48), alloc(12 * 4096), alloc(4 * 4096)
+before = fake.fake_used()
+for room in (filled + (1 << 20), filled - 1, 3 * n_p * n_p * 4):
+    fake.fake_limit(before + room)
+    s, h = create()
+    kernel, same = None, None
+    if s == 0:
+        if DATA:
+            # the maps as the kernels read them, at the stored width
+            buf = (ctypes.c_ubyte * (1 << 20))()
+            n = fake.fake_copied(buf)
+            DS = 8 if lib.sqn_cache_device_bytes(h) == filled else 4
+            want = np.zeros((9 * DS + 3, DS), np.float32)
+            want[:9 * DS].reshape(3, 3, DS, DS)[:, :, :D, :D] = w[1].reshape(3, D, 3, D).transpose(0, 2, 3, 1)
+            want[9 * DS:, :D] = w[2].reshape(3, D)
+            same = n == want.nbytes and bytes(buf[:n]) == want.tobytes()
+        fake.fake_reset()
+        assert lib.sqn_render(h, poses, 1, ctypes.byref(it), 0.5, 1.0, 64, rgb, depth, None) == 0
+        kernel = int(re.search(r"render_kernelI\w+?Li(\d+)ELb0E", launches()[0]).group(1))
+        bytes_ = lib.sqn_cache_device_bytes(h)
+        lib.sqn_destroy(h)
+    else:
+        assert not h.value
+        bytes_ = 0
+    out["tries"].append([s, kernel, bytes_, same, fake.fake_used() - before])
+print(json.dumps(out))
+""", data=linear)
+    first, short, none = got["tries"]
+    assert first[:3] == [0, 8, got["filled"]] and first[4] == 0
+    narrow = got["filled"] - 3 * 64 * 64 * 12 * 2 - 256 * 4 * 2
+    if linear:
+        narrow = short[2]       # its maps are smaller too
+        assert 0 < narrow < got["filled"] - 3 * 64 * 64 * 12 * 2
+        assert first[3] and short[3]
+    assert short[:3] == [0, 0, narrow] and short[4] == 0
+    assert none[0] == 2 and none[4] == 0       # SQN_ERR_OUT_OF_MEMORY
