@@ -474,8 +474,8 @@ size_t prepare_work(const sqn_cache_desc* desc, bool linear, char* base, sqn::Pr
 // a handle's block.  The copies fill them last, so until then the preparation
 // takes its scratch there: no second allocation on a load (hipMalloc and
 // hipFree of one cost 60-100 us of a 512 cache's 430), and none at all on a
-// recreate.  It fits unless a linear decoder has few components (D = 1) or a
-// small grid.
+// recreate.  Eq. 4's always fits; Eq. 5's, which holds the folded sums too, does
+// unless the grid is small or its records narrow (kept at few components).
 size_t late_bytes(const CacheLayout& lay) { return lay.off_lin - lay.off_uvw[0]; }
 
 // ---- copies ------------------------------------------------------------------
@@ -777,7 +777,8 @@ sqn_status create_impl(const sqn_cache_desc* desc, const sqn_linear_decoder* dec
     return SQN_OK;
 }
 
-// The largest grid sqn_recreate_caches takes.
+// The largest grid sqn_recreate_caches takes: the call's contract, nothing in
+// the preparation (which takes n_p up to 8192) depends on it.
 constexpr int32_t kRecreateMaxNp = 2048;
 
 // ---- cache generation: networks on the host side ---------------------------
@@ -910,7 +911,7 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     if (!sigma_planes || !uvw_planes)
         return fail(SQN_ERR_INVALID_ARG, "plane pointer array is NULL");
     if (desc->n_p > kRecreateMaxNp)
-        return fail(SQN_ERR_INVALID_ARG, "n_p = %d exceeds %d, the largest grid the preparation's scratch covers",
+        return fail(SQN_ERR_INVALID_ARG, "n_p = %d exceeds %d, the largest grid a recreate takes, whatever scratch its block has room for",
                     desc->n_p, kRecreateMaxNp);
     int device = -1;
     if (hipGetDevice(&device) != hipSuccess)
@@ -937,13 +938,14 @@ sqn_status sqn_recreate_caches(sqn_caches* caches, const sqn_cache_desc* desc,
     if ((s = check_device_range(beta, lay.beta_bytes / lay.D * desc->D, "beta")) != SQN_OK)
         return s;
 
-    // the scratch lies where the uvw planes and the direction cache go; every
-    // kernel of the preparation writes its whole array before it is read, so
-    // nothing needs clearing
+    // the scratch lies where the uvw planes and the direction cache go (it
+    // always fits: 3.2 bytes per texel against at least 18 of the planes, and
+    // the smallest grids against their regions' 256 bytes); every kernel of
+    // the preparation writes its whole array before it is read, so nothing
+    // needs clearing
     char* base = static_cast<char*>(caches->block);
     sqn::PrepareWork pw;
-    if (prepare_work(desc, false, base + lay.off_uvw[0], &pw) > late_bytes(lay))
-        return fail(SQN_ERR_UNSUPPORTED, "the preparation's scratch does not fit the handle's block");
+    prepare_work(desc, false, base + lay.off_uvw[0], &pw);
     hipStream_t st = static_cast<hipStream_t>(stream);
     void* const packed[3] = {base + lay.off_sigma[0], base + lay.off_sigma[1], base + lay.off_sigma[2]};
     hipError_t e = sqn::prepare_sigma_planes(sigma_planes, desc->sigma_dtype, desc->n_p, packed, pw, st);

@@ -103,7 +103,7 @@ int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, void** s)
 }
 
 /* launches: the log, and the clock they advance */
-static char log_[1 << 20];
+static char log_[1 << 22];
 static size_t log_len;
 static struct { char part[64]; double ms; } costs[64];
 static int n_costs;
@@ -118,7 +118,7 @@ void fake_cost(const char* part, double ms)
 
 int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t n, void* s)
 {
-    (void)args, (void)n, (void)s;
+    (void)n, (void)s;
     const char* name = "?";
     for (int k = 0; k < n_kernels; ++k)
         if (kernels[k].host == f)
@@ -130,6 +130,11 @@ int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t n, void* 
         return fail(INVALID_CONFIGURATION);
     if (log_len < sizeof(log_) - 512)
         log_len += (size_t)snprintf(log_ + log_len, 512, "%s %u %u %u %u\n", name, g.x, g.y, g.z, b.x);
+    if (strstr(name, "row_distance") && log_len < sizeof(log_) - 512)
+        /* its scratch: (live, f, f_min, n_p, pitch) */
+        log_len += (size_t)snprintf(log_ + log_len, 512, "scratch %llu %llu %d %d\n",
+                                    (unsigned long long)*(uintptr_t*)args[1],
+                                    (unsigned long long)*(uintptr_t*)args[2], *(int*)args[3], *(int*)args[4]);
     for (int k = 0; k < n_costs; ++k)
         if (strstr(name, costs[k].part)) {
             now += costs[k].ms;

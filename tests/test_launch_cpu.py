@@ -194,3 +194,34 @@ print(json.dumps(out))
         assert first[3] and short[3]
     assert short[:3] == [0, 0, narrow] and short[4] == 0
     assert none[0] == 2 and none[4] == 0       # SQN_ERR_OUT_OF_MEMORY
+
+
+def test_recreate_scratch_lies_in_the_block():
+    """The preparation's row distances and their minima end inside the handle's
+    block, behind its sigma records, for every small grid and the largest,
+    with the narrowest records there are."""
+    got = fake_hip.run(r"""
+import re
+out = []
+for n_p in list(range(2, 130)) + [255, 256, 257, 1023, 1025, 2047, 2048]:
+    for D, uvw in ((1, "f16"), (1, "f32"), (2, "f32"), (3, "f16")):
+        d = desc(n_p, D, n_theta=2, n_phi=2, uvw=uvw)
+        a = arrays(d)
+        h = ctypes.c_void_p()
+        assert lib.sqn_create_caches(ctypes.byref(d), a[0], a[1], a[2], None, ctypes.byref(h)) == 0
+        fake.fake_reset()
+        assert lib.sqn_recreate_caches(h, ctypes.byref(d), a[0], a[1], a[2], None) == 0
+        f, f_min, n, pitch = [int(x) for x in [l for l in launches() if l.startswith("scratch")][0].split()[1:]]
+        base, size = ctypes.c_void_p(), ctypes.c_size_t()
+        fake.hipMemGetAddressRange(ctypes.byref(base), ctypes.byref(size), ctypes.c_void_p(f))
+        sigma = 3 * -(-(4 * n_p * (-(-n_p // 4) * 4)) // 256) * 256      # 4-byte records, rows padded to four
+        rows = -(-n_p // 16)
+        ok = (n == n_p and size.value == lib.sqn_cache_device_bytes(h) and base.value + sigma <= f
+              and f + 3 * rows * 16 * pitch <= f_min and f_min + 3 * rows * pitch <= base.value + size.value)
+        if not ok:
+            out.append([n_p, D, uvw, f - base.value, f_min - base.value, pitch, size.value])
+        lib.sqn_destroy(h)
+        free(a)
+print(json.dumps(out))
+""")
+    assert got == []

@@ -1,6 +1,6 @@
 """sqn_recreate_caches, the entry point for callers that cannot allocate:
 new Eq. 4 caches written into an existing handle's device memory with the
-create-time preparation in the library's static scratch.  Its renders must
+create-time preparation in the handle's own block.  Its renders must
 be bit for bit those of a handle made by sqn_create_caches from the same
 arrays, on two calls in a row, the second with a smaller grid."""
 import ctypes
@@ -120,7 +120,7 @@ def test_recreate_rejects_what_the_handle_cannot_hold():
         # a layout larger than the handle's block
         st = binding.lib.sqn_recreate_caches(handle.handle, ctypes.byref(desc), sp, up, bp, stream)
         assert st == binding.SQN_ERR_INVALID_ARG and "holds" in binding.last_error()
-        # a grid beyond the static scratch
+        # a grid beyond the call's limit
         desc.n_p = 4096
         st = binding.lib.sqn_recreate_caches(handle.handle, ctypes.byref(desc), sp, up, bp, stream)
         assert st == binding.SQN_ERR_INVALID_ARG and "scratch" in binding.last_error()
