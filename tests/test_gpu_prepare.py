@@ -1,14 +1,16 @@
 """Create-time preparation at the sizes where its tiles, caps and remainders
-can go wrong: a march that leaps by the distance fields (and the linear
-decoder's cell grid) must find the very samples that a dense march of the
-same handle finds, which reads no distance.  A distance one too large, a
-record in the wrong place or a copy that stops short shows as another hash,
-count or colour; sparse planes make the distances reach the 255-texel cap.
+can go wrong.  Distances: a march that leaps by the distance fields (and the
+linear decoder's cell grid) must find the very samples that a dense march of
+the same handle finds, which reads no distance; sparse planes make the
+distances reach the 255-texel cap.  Records and copies, which both marches
+read: whole frames against the CPU oracle, which reads the caller's arrays.
 """
 import numpy as np
 import pytest
 
+import oracle
 from paper_2204_02585_amd import scenes
+from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
 
@@ -142,3 +144,55 @@ def test_arrays_that_start_between_16_byte_pieces(shift):
         finally:
             caches.close()
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+def _against_oracle(sig, uvw, beta, decoder, label):
+    """A small frame of these arrays (numpy, in their storage types) with the
+    handle's records against the oracle's, every ray and statistic."""
+    import torch
+    from paper_2204_02585_amd import binding
+    intr = dict(fx=30.0, fy=30.0, cx=12.0, cy=9.5, width=24, height=19)
+    poses, n = scenes.spiral_poses(2), 96
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    caches = binding.Caches([dev(a) for a in sig], [dev(a) for a in uvw], dev(beta), scenes.BOX_MIN, scenes.BOX_MAX,
+                            decoder=decoder)
+    try:
+        rgb, depth, st = caches.render_stats(dev(poses), intr, 2.0, 6.0, n)
+        torch.cuda.synchronize()
+    finally:
+        caches.close()
+    ref = oracle.render(sig, uvw, beta, poses, intr, 2.0, 6.0, n, scenes.BOX_MIN, scenes.BOX_MAX, decoder=decoder)
+    assert int(ref["n_occ"].sum()) > 0, label
+    gpu = (rgb.cpu().numpy().reshape(-1, 3), depth.cpu().numpy().reshape(-1),
+           st.cpu().numpy().view(np.uint32).reshape(-1, 4))
+    # binary32 values, sums in binary64
+    pu.compare(gpu, ref, np.arange(ref.size), 1e-5, label)
+
+
+def _arrays(n_p, rng, D, dtype, channels=0):
+    ndt = np.float16 if dtype == "f16" else np.float32
+    # the oracle takes finite values, as the entry point documents
+    sig = [np.nan_to_num(p).astype(ndt) for p in _planes(n_p, rng, 0.05, channels)]
+    uvw = [rng.uniform(-1, 1, (n_p, n_p, 3 * D)).astype(ndt) for _ in range(3)]
+    return sig, uvw, rng.uniform(-1, 1, (3, 5, D)).astype(ndt)
+
+
+# the copies' runs of 32 KiB: whole ones with a tail (67, 129, 257), a part of
+# one (2, 17), none left over (256); records filled up and as they are
+@pytest.mark.parametrize("n_p", [2, 17, 67, 129, 256, 257])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_records_and_copies(n_p, dtype):
+    rng = np.random.Generator(np.random.PCG64(2000 + n_p))
+    for D in (1, 3, 8, 16):
+        _against_oracle(*_arrays(n_p, rng, D, dtype), None, f"records n_p={n_p} D={D} {dtype}")
+
+
+@pytest.mark.parametrize("n_p", [2, 17, 64, 130, 257])
+@pytest.mark.parametrize("channels,dtype", [(1, "f32"), (12, "f16"), (64, "f32"), (64, "f16")])
+def test_folded_records(n_p, channels, dtype):
+    rng = np.random.Generator(np.random.PCG64(3000 * channels + n_p))
+    for D in (1, 8):
+        dec = scenes.LinearDecoder(rng.uniform(2.0, 3.0, 3 * channels).astype(np.float32), -3.6 * channels,
+                                   rng.uniform(-0.3, 0.3, (3, D, 3 * D)).astype(np.float32),
+                                   rng.uniform(-0.1, 0.1, (3, D)).astype(np.float32))
+        _against_oracle(*_arrays(n_p, rng, D, dtype, channels), dec, f"folded n_p={n_p} D={D} {channels} {dtype}")
