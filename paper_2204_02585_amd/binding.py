@@ -229,6 +229,14 @@ def _order_after_current(stream, *tensors) -> None:
                 t.record_stream(stream)
 
 
+def _empty(poses: torch.Tensor, shape) -> torch.Tensor:
+    """A plain binary32 tensor beside `poses` (new_empty, the quicker call,
+    would give a subclass of Tensor its like)."""
+    if type(poses) is torch.Tensor:
+        return poses.new_empty(shape)
+    return torch.empty(shape, dtype=torch.float32, device=poses.device)
+
+
 class Caches:
     """Library-owned device copy of the SqueezeNeRF caches (sqn_create_caches,
     or sqn_create_linear_caches when `decoder` is given: an object with
@@ -352,13 +360,13 @@ class Caches:
         B, device = poses.shape[0], poses.device
         H, W = int(intrinsics["height"]), int(intrinsics["width"])
         if rgb_out is None:
-            rgb_out = poses.new_empty((B, H, W, 3))
+            rgb_out = _empty(poses, (B, H, W, 3))
         else:
             _output_arg(rgb_out, (B, H, W, 3), device, "rgb_out")
         if depth_out is not None:
             _output_arg(depth_out, (B, H, W), device, "depth_out")
         elif with_depth:
-            depth_out = poses.new_empty((B, H, W))
+            depth_out = _empty(poses, (B, H, W))
         if stream is None:
             on = _current_stream()
         else:
