@@ -22,8 +22,11 @@ __host__ __device__ inline float opacity(float q)
 {
     const float x = q > 64.0f ? -64.0f : -q;
     // adding 1.5 * 2^23 rounds to the nearest integer, which is then in the
-    // low bits of the sum
-    const float t = fmaf(x, 1.44269502162933349609375f, 12582912.0f);
+    // low bits of the sum (a product and a sum, each with its constant in the
+    // instruction: a fused one keeps one of the two in a register across the
+    // march, which cost some kernels a wave)
+    const float y = x * 1.44269502162933349609375f;
+    const float t = y + 12582912.0f;
     const float n = t - 12582912.0f;
     float r = fmaf(n, -0.693145751953125f, x);       // 16 bits: n times it is exact
     r = fmaf(n, -1.42860682030941723212e-6f, r);

@@ -83,3 +83,14 @@ def test_marches_that_lost_to_spills_spill_nothing(render_object):
     for name in (_kernel("f32", "f16", 8, 1, ndc=True), hybrid):
         vgprs, scratch = found[name]
         assert vgprs <= 72 and scratch == 0, (name, vgprs, scratch)
+
+
+def test_opacity_keeps_no_constant_in_a_register(render_object):
+    """One register more across the march costs these a wave per SIMD (two
+    lanes, binary16 sigma and binary32 uvw: 80 of 80) or a spill (Eq. 5,
+    binary32, D = 8: 96 of 96)."""
+    found = _resources(render_object)
+    eq5 = "_ZN3sqn12_GLOBAL__N_113render_kernelIffLi8ELb0ELi4ELb1ELb1ELb0EEEvNS_12RenderParamsE"
+    for name, most in ((_kernel("f16", "f32", 8, 2), 80), (eq5, 96)):
+        vgprs, scratch = found[name]
+        assert vgprs <= most and scratch == 0, (name, vgprs, scratch)
