@@ -225,3 +225,49 @@ for n_p in list(range(2, 130)) + [255, 256, 257, 1023, 1025, 2047, 2048]:
 print(json.dumps(out))
 """)
     assert got == []
+
+
+def test_every_direction_grid_is_a_legal_launch():
+    """Generation and creation over the direction grids that validation accepts,
+    up to 2^31 nodes of D = 1: the launches stay within 2^32 work items per
+    dimension (the stand-in for the runtime refuses others), and all nodes are
+    covered."""
+    grids = [(2, 2), (192, 256), (193, 256), (4096, 4096), (16384, 16383), (16384, 16384), (20000, 20000),
+             (65536, 32767), (44431, 48333)]
+    got = fake_hip.run(r"""
+import numpy as np
+def mlp(sizes):
+    m = B.MLPDesc()
+    m.n_hidden, m.width, m.n_in, m.n_out = len(sizes) - 2, sizes[1], sizes[0], sizes[-1]
+    ws = [np.zeros((o, i), np.uint16) for i, o in zip(sizes[:-1], sizes[1:])]
+    bs = [np.zeros(o, np.float32) for o in sizes[1:]]
+    w = (ctypes.c_void_p * len(ws))(*[x.ctypes.data for x in ws])
+    b = (ctypes.c_void_p * len(bs))(*[x.ctypes.data for x in bs])
+    m.weights, m.biases = ctypes.cast(w, type(m.weights)), ctypes.cast(b, type(m.biases))
+    return m, (ws, bs, w, b)
+out = []
+D = 1
+pos, keep = zip(*[mlp([2 * (1 + 2 * 10), 256, 2 + 6 * D]) for _ in range(3)])
+dirn, keep_d = mlp([3 * (1 + 2 * 4), 128, D])
+nets = ctypes.c_void_p()
+assert lib.sqn_create_networks((B.MLPDesc * 3)(*pos), ctypes.byref(dirn), D, 10, 4, None, ctypes.byref(nets)) == 0
+for nt, nph in DATA:
+    for n_p in (8, 128):
+        d = desc(n_p, D, n_theta=nt, n_phi=nph)
+        a = arrays(d)
+        fake.fake_reset()
+        s = lib.sqn_generate_caches(nets, ctypes.byref(d), a[0], a[1], a[2], None)
+        log = [l.split() for l in launches()]
+        own = [l for l in log if "direction_kernel" in l[0]]
+        nodes = sum(int(l[1]) * int(l[2]) * 128 for l in own)
+        h = ctypes.c_void_p()
+        c = lib.sqn_create_caches(ctypes.byref(d), a[0], a[1], a[2], None, ctypes.byref(h))
+        lib.sqn_destroy(h)
+        out.append([nt, nph, n_p, s, c, len(own), nodes])
+        free(a)
+print(json.dumps(out))
+""", data=grids)
+    for nt, nph, n_p, s, c, own, nodes in got:
+        assert s == 0 and c == 0, (nt, nph, n_p, s, c)
+        assert own == (1 if nt * nph > 49152 else 0), (nt, nph, n_p, own)
+        assert own == 0 or nodes >= nt * nph
